@@ -15,14 +15,15 @@
 //   K6 k_blend_fwd      per tile: front-to-back compositing, Eq. 11 with clamp/skip/stop
 //   K7 k_loss_l1        Eq. 12 (mean L1 colour) + weighted mean L1 depth, its gradient
 //   K8 k_blend_bwd2     per (tile, stride) item, back to front: transmittance recovered by
-//      (k_blend_bwd)    division, per-(pixel, splat) partials of two pixels per lane
+//                       division, per-(pixel, splat) partials of two pixels per lane
 //                       (one for tiles of 8) reduced across the wavefront with DPP, summed
 //                       per splat in LDS and added with float atomics, splat-major
 //   K9 k_project_bwd    per Gaussian, loop over views: chain rule to means, scales,
 //                       rotations, opacities and SH coefficients
 //
-// Nothing here is a dense contraction, so no MFMA: the per-Gaussian kernels are HBM
-// bound, the blend kernels VALU/transcendental bound.
+// The per-Gaussian kernels are HBM bound, the blend kernels VALU/transcendental bound; no
+// dense contraction, but the entry-by-pixel products of the blend kernels (offsets, colour
+// sums) run as rank-1 updates on the matrix cores.
 #include "gsr_internal.h"
 
 namespace gsr {
@@ -48,47 +49,6 @@ __device__ __forceinline__ void swap_rows(float& a, float& b) {
   const auto r = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(int, a), __builtin_bit_cast(int, b), false, false);
   a = __builtin_bit_cast(float, int(r[0]));
   b = __builtin_bit_cast(float, int(r[1]));
-}
-
-// Sums of ten per-lane values over the wavefront in 28 instructions: lane halves are folded
-// pairwise (5 swaps + 5 adds), then 16-lane rows (3 swaps + 3 adds), then each row is
-// reduced with 4 fused DPP adds.  Every lane of a row ends with its row's total:
-//   w0 rows 0..3 = sums of v0, v2, v1, v3;  w1 rows = v4, v6, v5, v7;  w2 rows = v8, v8, v9, v9.
-// Needs every lane active.
-__device__ __forceinline__ void wave_sum10(const float (&v)[10], float& w0, float& w1, float& w2) {
-  float u[5];
-#pragma unroll
-  for (int i = 0; i < 5; ++i) {
-    float a = v[2 * i], b = v[2 * i + 1];
-    swap_halves(a, b);
-    u[i] = a + b;
-  }
-  float a = u[0], b = u[1];
-  swap_rows(a, b);
-  w0 = a + b;
-  a = u[2];
-  b = u[3];
-  swap_rows(a, b);
-  w1 = a + b;
-  a = u[4];
-  b = u[4];
-  swap_rows(a, b);
-  w2 = a + b;
-  w0 += dpp_move<0xB1, 0xF>(w0);
-  w1 += dpp_move<0xB1, 0xF>(w1);
-  w2 += dpp_move<0xB1, 0xF>(w2);
-  w0 += dpp_move<0x4E, 0xF>(w0);
-  w1 += dpp_move<0x4E, 0xF>(w1);
-  w2 += dpp_move<0x4E, 0xF>(w2);
-  w0 += dpp_move<0x141, 0xF>(w0);
-  w1 += dpp_move<0x141, 0xF>(w1);
-  w2 += dpp_move<0x141, 0xF>(w2);
-  w0 += dpp_move<0x140, 0xF>(w0);
-  w1 += dpp_move<0x140, 0xF>(w1);
-  w2 += dpp_move<0x140, 0xF>(w2);
-  // the sums exist in every lane here, so the last adds stay with their DPP moves (fused)
-  // rather than sinking into the callers' one-lane-per-row stores
-  asm volatile("" : "+v"(w0), "+v"(w1), "+v"(w2));
 }
 
 // Rank-1 update on the matrix cores (v_mfma_f32_4x4x1, one block's A broadcast to all):
@@ -459,6 +419,13 @@ __device__ __forceinline__ void stage_record(const Records& rec, uint32_t id, fl
   my = g0.y;
   sq = make_float4(kNegHalfLog2e * g0.z, (2.f * kNegHalfLog2e) * g0.w, kNegHalfLog2e * g1.x, g1.y);
   col = make_float4(c.x, c.y, c.z, g1.z);
+}
+
+// Whether the alpha of a staged splat (a', b', c', o) is never clamped and always finite: o below
+// alpha_max by more than the rounding of exp2(q') <= 1, and a conic whose products with
+// pixel offsets (below 2^14) stay finite.  NaNs are not plain.
+__device__ __forceinline__ bool plain_splat(const float4& sq, float amax) {
+  return sq.w * 1.0001f <= amax && fabsf(sq.x) + fabsf(sq.y) + fabsf(sq.z) < 1e28f;
 }
 
 // ------------------------------------------------------------------------------------
@@ -1645,6 +1612,7 @@ constexpr int kFwdGroup = 16;
 // so that fewer long items are left running at the end of its launch (32 was slower:
 // each item has a fixed cost, its setup reads and staging, of some 10 us under load)
 constexpr int kCkptStride = 64;
+constexpr int kBwdGroup = 4;  // entries evaluated together by the backward compositing
 static_assert(128 % kFwdGroup == 0 && kCkptStride % kFwdGroup == 0 && 128 % kCkptStride == 0,
               "batches and checkpoint strides hold whole groups");
 
@@ -1903,11 +1871,10 @@ __global__ __launch_bounds__(256) void k_loss_sum(const float* part, int count, 
 // the item, else from the forward's checkpoint at the item's end.  So no wavefront walks
 // more than one checkpoint stride until a tile's checkpoints run out.
 //
-// Each wavefront walks the staged batch only down from its own longest contributor list.
-// The ten per-(pixel, splat) partials are summed across the wavefront with lane swaps
-// and DPP (wave_sum10); with more than one wavefront per tile the wavefront sums meet
-// in LDS and the block adds each splat's total to the 2D-gradient buffer once per item,
-// with the atomics spread over all lanes.
+// Each wavefront walks the staged entries only down from its own longest contributor list.
+// The seven per-lane partials of each splat are reduced across the wavefront to its ten
+// sums (splat_sums); the wavefronts' sums meet in LDS and the block adds each splat's total
+// to the 2D-gradient buffer once per item, a row at a time.
 
 // Block-uniform: the next backward work item, or -1; the first items (the heaviest
 // tiles) take a higher wave priority, as in the forward.
@@ -1927,7 +1894,7 @@ __device__ __forceinline__ int next_item(uint32_t* head, int total, int* s_item)
 }
 
 // K8 with PPL vertically adjacent pixels per lane: with two (tiles of 16 and 32) a
-// wavefront covers 128 pixels, so each splat's ten partials are reduced across the
+// wavefront covers 128 pixels, so each splat's partials are reduced across the
 // wavefront once for twice the pixels (the pair's partials are added first); tiles of 8
 // use one.  Two per lane is the build's choice for the larger tiles (kBwdPixelsPerLane);
 // four ran slower on the headline view.
@@ -1935,11 +1902,12 @@ __device__ __forceinline__ int next_item(uint32_t* head, int total, int* s_item)
 // Per pixel, back to front, with g = dL/d(colour, depth) of the pixel and B the blend of
 // g . (colour, depth) of the contributors behind (B = g . (bg, 0) behind the last):
 //   T_i = T_(i+1) / (1 - alpha_i),  dL/dalpha_i = T_i (g . (c_i, z_i) - B) + gA T_final / (1 - alpha_i),
-//   B <- alpha_i g . (c_i, z_i) + (1 - alpha_i) B,
+//   B <- B + alpha_i (g . (c_i, z_i) - B),
 // which is the per-channel recurrence of the colour behind, dotted with g once (g is fixed
-// per pixel).  The splat's geometric partials are kept as moments of q = a dL/da over the
-// pixel offsets, (sum q dx, sum q dy, sum q dx^2, sum q dx dy, sum q dy^2); the flush turns
-// them into the centre and conic gradients with the splat's conic, once per splat.
+// per pixel).  With w = alpha T and u = dL/da G (a = o G; zero where alpha is clamped) the
+// splat's gradients are sums over the pixels: colour and depth of w g, opacity of u, and
+// centre and conic of o times the offset moments of u, which the flush turns into
+// gradients with the splat's conic, once per splat.
 struct BwdPixel {
   float T, Tfin, gC0, gC1, gC2, gD, gATf, B, fpy;
   int top;
@@ -2002,94 +1970,131 @@ __device__ __forceinline__ void bwd_pixel_setup(BwdPixel& s, const ViewDev& cam,
   s.B = s.gC0 * BC0 + s.gC1 * BC1 + s.gC2 * BC2 + s.gD * BD;
 }
 
-// One (pixel, splat) step back to front, adding the pixel's partials to g: the five
-// geometric moments, dL/dopacity's sum of dL/da G, and the colour/depth weights.  A lane
-// that does not take part (past its list, or below the skip threshold) takes alpha = 0,
-// which leaves B unchanged and adds zeros; its T is kept by a select (1 / (1 - 0) is not
-// relied on to be exact).
-// Returns q = dL/da a, whose offset moments the caller forms (the pixels of a lane share dx).
-__device__ __forceinline__ float bwd_pixel_step(BwdPixel& s, bool act, float a, float G, const float4& r1,
-                                                const float4& c, const Rules& ru, float (&g)[10]) {
-  const bool below = a <= ru.amax;  // not clamped (shared by the clamp and its gradient)
-  const float al = act ? (below ? a : ru.amax) : 0.f;
-  const float om = 1.f - al;
-  const float iom = __builtin_amdgcn_rcpf(om);
-  s.T = s.T * iom;  // a lane that does not take the entry has om = 1, iom = 1 exactly
-  const float wgt = al * s.T;
-  g[6] += s.gC0 * wgt;
-  g[7] += s.gC1 * wgt;
-  g[8] += s.gC2 * wgt;
-  g[9] += s.gD * wgt;
-  const float S = s.gC0 * c.x + s.gC1 * c.y + s.gC2 * c.z + s.gD * r1.z;
-  const float dal = s.T * (S - s.B) + s.gATf * iom;
-  s.B = al * S + om * s.B;
-  const float da = (act && below) ? dal : 0.f;
-  g[5] += da * G;
-  return da * a;
+// Sums over the wavefront of a splat's seven per-lane partials, taken to the ten values of
+// its gradient in 22 instructions.  q, qy, qyy are the lane's moments of u over y (offsets
+// from the splat's centre), c0..c2 and z its colour and depth sums; dx is the lane's x offset,
+// the same in all lanes 16 apart (a tile's columns repeat every 8 or 16 lanes).  Lane halves
+// are folded pairwise (4 swaps and adds), then 16-lane rows (2); the x moments are formed on
+// those column sums; then the four registers are folded into one, 8 lanes and 4 lanes apart,
+// each add writing only its half's banks of four lanes (the DPP bank mask), and reduced over
+// the last four.  The four lanes of bank b in row r end with value 4 r + b:
+//   0 sum u, 1 u dx, 2 c1, 3 u dx^2 | 4 u dy^2, 6 z | 8 u dy, 9 u dx dy, 10 c2 | 12 c0
+// (the others hold nothing of use).  Needs every lane active.
+constexpr int kSumU = 0, kSumUx = 1, kSumC1 = 2, kSumUxx = 3, kSumUyy = 4, kSumZ = 6, kSumUy = 8, kSumUxy = 9,
+              kSumC2 = 10, kSumC0 = 12;
+
+__device__ __forceinline__ float splat_sums(float q, float qy, float qyy, float c0, float c1, float c2, float z,
+                                            float dx) {
+  auto fold_halves = [](float a, float b) {  // lanes 0-31: a summed 32 apart; lanes 32-63: b
+    swap_halves(a, b);
+    return a + b;
+  };
+  auto fold_rows = [](float a, float b) {  // even rows: a summed 16 apart; odd rows: b
+    swap_rows(a, b);
+    return a + b;
+  };
+  const float r0 = fold_rows(fold_halves(q, qy), fold_halves(qyy, c0));  // rows: q, qyy, qy, c0
+  const float r1 = fold_rows(fold_halves(c1, c2), fold_halves(z, z));    // rows: c1, z, c2, z
+  const float r2 = r0 * dx, r3 = r2 * dx;                                // q dx, -, qy dx, - | q dx^2, -, -, -
+  float f0, f1, g;
+  // (a DPP operand needs two instructions between its write and its use)
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "s_nop 0\n\t"
+      "v_add_f32_dpp %2, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
+      "s_nop 1\n\t"
+      "v_add_f32_dpp %2, %2, %2 quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf"
+      : "=&v"(f0), "=&v"(f1), "=&v"(g)
+      : "v"(r0), "v"(r1), "v"(r2), "v"(r3));
+  return g;
 }
 
-// The splat-major flush of a batch's per-splat sums (s_g: ten per splat and wavefront,
-// each wavefront writing only its own; summed over the wavefronts and cleared as they are
-// read) into the 2D-gradient rows: the lanes of a wavefront add consecutive sums of a
-// few splats, so one atomic instruction touches a few gradient rows (cache lines), not 64.
-// The moments become gradients here: with the staged conic (a', b', c') = (A, 2B, C) (-log2 e / 2),
-// (A dx + B dy, B dx + C dy) = -ln 2 (2a' dx + b' dy, b' dx + 2c' dy), so
-//   dmu = -ln 2 (2a' Mx + b' My, b' Mx + 2c' My),  d(A, B, C) = -(Mxx / 2, Mxy, Myy / 2).
+// The flush of a stage's sums (s_g: sixteen slots per splat and wavefront) into the 2D-gradient
+// rows.  One lane per splat adds up the wavefronts that hit it (s_hit; with eight of them, a
+// pass over all threads before) and turns the moments into gradients: with the staged conic
+// (a', b', c') = (A, 2B, C) (-log2 e / 2), (A dx + B dy, B dx + C dy) =
+// -ln 2 (2a' dx + b' dy, b' dx + 2c' dy), so
+//   dmu = -ln 2 o (2a' Ux + b' Uy, b' Ux + 2c' Uy),  d(A, B, C) = -o (Uxx / 2, Uxy, Uyy / 2).
+// Then the values are added splat-major: consecutive lanes take consecutive values of a few
+// rows, so one atomic instruction touches a few rows (cache lines), and a row's ten values
+// go out together.  (Atomics are carried out at the memory side, where their number counts:
+// with the centre's two values issued apart from the others the kernel took 170 us over
+// one 876x584 view of a 170k map, together 130.)
 template <int NT, int NW, int SB>
-__device__ __forceinline__ void flush_splat_sums(float (&s_g)[NW][SB][10], const uint32_t* s_id, const float4* s_r0,
-                                                 const float4* s_r1, const float4* s_rgb, int nstage,
-                                                 float* grad2d) {
+__device__ __forceinline__ void flush_splat_sums(float (&s_g)[NW][SB][16], const uint64_t (&s_hit)[NW],
+                                                 const uint32_t* s_id, const float4* s_q, int nstage, float* grad2d) {
   constexpr float kNegLn2 = -0.69314718055994531f;
-  // the wavefronts' sums of slot (j, k), cleared as they are read
-  auto take = [&](int j, int k) {
-    float v = 0.f;
+  if constexpr (NW > 2) {
+    for (int i = threadIdx.x; i < 16 * nstage; i += NT) {
+      const int j = i >> 4, k = i & 15;
+      float v = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      v += s_g[w][j][k];
-      s_g[w][j][k] = 0.f;
+      for (int w = 0; w < NW; ++w) v += (s_hit[w] >> j) & 1ull ? s_g[w][j][k] : 0.f;
+      s_g[0][j][k] = v;
     }
-    return v;
-  };
+    __syncthreads();
+  }
+  for (int j = threadIdx.x; j < nstage; j += NT) {
+    auto sum = [&](int k) {
+      if constexpr (NW > 2) return s_g[0][j][k];
+      float v = (s_hit[0] >> j) & 1ull ? s_g[0][j][k] : 0.f;
+      if constexpr (NW == 2) v += (s_hit[1] >> j) & 1ull ? s_g[1][j][k] : 0.f;
+      return v;
+    };
+    const float4 sq = s_q[j];
+    const float ol = sq.w * kNegLn2, ux = sum(kSumUx), uy = sum(kSumUy);
+    const float v[10] = {ol * (2.f * sq.x * ux + sq.y * uy),
+                         ol * (sq.y * ux + 2.f * sq.z * uy),
+                         -0.5f * sq.w * sum(kSumUxx),
+                         -sq.w * sum(kSumUxy),
+                         -0.5f * sq.w * sum(kSumUyy),
+                         sum(kSumU),
+                         sum(kSumC0),
+                         sum(kSumC1),
+                         sum(kSumC2),
+                         sum(kSumZ)};
+#pragma unroll
+    for (int k = 0; k < 10; ++k) s_g[0][j][k] = v[k];
+  }
+  __syncthreads();
   for (int i = threadIdx.x; i < 10 * nstage; i += NT) {
     const int j = i / 10, k = i - 10 * j;
-    if (k == 1) continue;  // the centre's y gradient goes with its x gradient (k == 0)
-    float* dst = grad2d + int64_t(s_id[j]) * kGrad2D;
-    if (k == 0) {
-      const float mx = take(j, 0), my = take(j, 1);
-      if (mx != 0.f || my != 0.f) {
-        const float b = s_r0[j].w;   // b'
-        const float a2 = s_r1[j].w;  // 2 a'
-        const float c2 = s_rgb[j].w; // 2 c'
-        unsafeAtomicAdd(dst, kNegLn2 * (a2 * mx + b * my));
-        unsafeAtomicAdd(dst + 1, kNegLn2 * (b * mx + c2 * my));
-      }
-      continue;
-    }
-    const float v = take(j, k);
-    if (v != 0.f) unsafeAtomicAdd(dst + k, k == 3 ? -v : ((k == 2 || k == 4) ? -0.5f * v : v));
+    const float v = s_g[0][j][k];
+    if (v != 0.f) unsafeAtomicAdd(grad2d + int64_t(s_id[j]) * kGrad2D + k, v);
   }
 }
 
-template <int TS, int BATCH, int PPL>
-__global__ __launch_bounds__(TS* TS / PPL) void k_blend_bwd2(ViewTable vt, Rules ru, Records rec,
+template <int TS, int PPL>
+__global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS == 32 ? 4 : 5))) void k_blend_bwd2(ViewTable vt, Rules ru, Records rec,
                                                             const uint2* ranges, const uint32_t* vals,
                                                             const float* T_final, const uint32_t* n_contrib,
                                                             float* grad2d, TileQueue q, Ckpt ck) {
-  constexpr int NT = TS * TS / PPL;  // threads: pixels (PPL r + i, c), i < PPL, for t = r TS + c
+  constexpr int NT = TS * TS / PPL;  // threads
   constexpr int NW = NT / 64;        // wavefronts
+  constexpr int WX = TS < 16 ? TS : 16;  // a wavefront's pixels: WX wide, 8 high (splat_sums needs
+  static_assert(64 * PPL == 8 * WX, "");  // lanes 16 apart in one column)
   constexpr int SB = kCkptStride;    // entries staged at a time: one checkpoint stride
-  __shared__ float4 s_r0[SB];
-  __shared__ float4 s_r1[SB];
-  __shared__ float4 s_rgb[SB];
+  constexpr int GS = kBwdGroup;
+  static_assert(SB % GS == 0 && GS % 4 == 0, "a stage holds whole groups, a group whole matrix operands");
+  __shared__ float2 s_mu[SB];           // splat centres
+  __shared__ float4 s_q[SB];            // a', b', c', opacity
+  __shared__ float s_c[4][SB];          // colour, depth
   __shared__ uint32_t s_id[SB];
-  __shared__ float s_g[NW][SB][10];  // per wavefront and staged splat, its ten sums
+  __shared__ float s_g[NW][SB][16];     // per wavefront and staged splat it hit, its sums (splat_sums)
+  __shared__ uint64_t s_hit[NW];        // per wavefront, the staged splats some pixel of it takes
   __shared__ uint32_t s_max;
   __shared__ int s_item;
-  for (int i = threadIdx.x; i < NW * 10 * SB; i += NT) (&s_g[0][0][0])[i] = 0.f;
   const int wv = int(threadIdx.x) >> 6;
   const int total = int(q.ctrl[kItems]);
   const int lane = threadIdx.x & 63;
-  const int cx = int(threadIdx.x % TS), ry = PPL * int(threadIdx.x / TS);
+  // this lane's pixels within the tile: column cx, rows ry .. ry + PPL - 1
+  const int cx = WX * (wv % (TS / WX)) + lane % WX, ry = 8 * (wv / (TS / WX)) + PPL * (lane / WX);
   for (;;) {
     const int item = next_item(q.ctrl + kHeadBwd, total, &s_item);
     if (item < 0) return;
@@ -2121,58 +2126,116 @@ __global__ __launch_bounds__(TS* TS / PPL) void k_blend_bwd2(ViewTable vt, Rules
       const int bstart = max(lo, bend - SB);
       const int nstage = bend - bstart;
       __syncthreads();
+      int odd = 0;
       for (int j = threadIdx.x; j < nstage; j += NT) {
         const uint32_t id = vals[rg.x + bstart + j];
+        float mx, my;
+        float4 sq, sc;
+        stage_record(rec, id, mx, my, sq, sc);
+        odd |= !plain_splat(sq, ru.amax);
         s_id[j] = id;
-        stage_record(rec, id, s_r0[j], s_r1[j], s_rgb[j]);
+        s_mu[j] = make_float2(mx, my);
+        s_q[j] = sq;
+        s_c[0][j] = sc.x;
+        s_c[1][j] = sc.y;
+        s_c[2][j] = sc.z;
+        s_c[3][j] = sc.w;
       }
-      __syncthreads();
-      for (int j = min(nstage, wmax - bstart) - 1; j >= 0; --j) {
-        const float4 r0 = s_r0[j];
-        const float4 r1 = s_r1[j];
-        const float dx = fpx - r0.x;
-        float dy[PPL], a[PPL], G[PPL];
-        bool act[PPL];
-        bool any = false;
+      const bool plain = __syncthreads_or(odd) == 0;  // no pixel clamps a staged splat's alpha
+      // Groups of staged entries, back to front.  First everything that does not depend on the
+      // running T and B, for the whole group at once (its LDS reads and exponentials overlap);
+      // g . (colour, depth) as rank-1 updates on the matrix cores (four entries each).  Then the recurrences and sums, entry by entry;
+      // entries that no pixel of the wavefront takes are left out.  A lane that does not take
+      // an entry (past its list or the stage, or below the skip threshold) has alpha = 0, which
+      // leaves T and B unchanged (1 / (1 - 0) = 1 exactly) and gives u = w = 0.
+      //
+      // The kernel is bound by VALU issue where many items are in flight, and by its items'
+      // latency where few are; measured issue costs per wavefront instruction are 2 cycles for
+      // adds, multiplies and fmas, 4 for compares, selects, min and DPP, 8 for exponentials,
+      // reciprocals, lane swaps and the 4x4x1 products.  Against one entry at a time, an alpha
+      // clamp on every entry and centre atomics of their own: 15.7 -> 12.9 ms over sixteen
+      // 1752x1168 views, 1105 -> 925 us over eight uneven ones, 175 -> 124 us and 149 -> 122 us on
+      // one 876x584 (170k splats) and one 640x480 view (500k).  Taking the sums as matrix products
+      // (16x16x4, splats by pixels) was slower over many views (19.4 ms): they share the
+      // VALU's issue at 32 cycles each and need 30 KB of LDS a block.
+      uint64_t hit = 0;  // staged splats some pixel of the wavefront takes (wavefront-uniform)
+      for (int jb = (min(nstage, wmax - bstart) - 1) & ~(GS - 1); jb >= 0; jb -= GS) {
+        const int je = jb + (lane & (GS - 1));
+        const float e0 = s_c[0][je], e1 = s_c[1][je], e2 = s_c[2][je], e3 = s_c[3][je];
+        float G[GS][PPL], o[GS];  // (alpha before the clamp is o G)
+        bool act[GS][PPL];
+        float dx[GS], dy0[GS];
+        f32x4 S[GS / 4][PPL];
+        uint32_t hits = 0;
+        int lim[PPL];  // the pixels' entries of this group
 #pragma unroll
         for (int i = 0; i < PPL; ++i) {
-          dy[i] = p[i].fpy - r0.y;
-          a[i] = splat_alpha(dx, dy[i], r0.z, r0.w, r1.x, r1.y, G[i]);
-          act[i] = bstart + j < p[i].top && !(a[i] < ru.amin);
-          any = any || act[i];
-        }
-        if (__ballot(any) == 0ull) continue;
-        const float4 c = s_rgb[j];
-        float gv[10] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        // the offset moments of the lane's pixels (one column: one dx): Σq, Σq dy, Σq dy²,
-        // then Σq dx = dx Σq, Σq dx² = dx² Σq, Σq dx dy = dx Σq dy
-        float Q = 0.f, QY = 0.f, QYY = 0.f;
+          lim[i] = min(p[i].top, bend) - (bstart + jb);
 #pragma unroll
-        for (int i = 0; i < PPL; ++i) {
-          const float q = bwd_pixel_step(p[i], act[i], a[i], G[i], r1, c, ru, gv);
-          const float qy = q * dy[i];
-          Q = i == 0 ? q : Q + q;
-          QY = i == 0 ? qy : QY + qy;
-          QYY = i == 0 ? qy * dy[i] : QYY + qy * dy[i];
+          for (int h = 0; h < GS / 4; ++h) {
+            S[h][i] = mfma_rank1(e0, p[i].gC0, f32x4{0.f, 0.f, 0.f, 0.f}, h);
+            S[h][i] = mfma_rank1(e1, p[i].gC1, S[h][i], h);
+            S[h][i] = mfma_rank1(e2, p[i].gC2, S[h][i], h);
+            S[h][i] = mfma_rank1(e3, p[i].gD, S[h][i], h);
+          }
         }
-        const float Qx = Q * dx;
-        gv[0] = Qx;
-        gv[1] = QY;
-        gv[2] = Qx * dx;
-        gv[3] = QY * dx;
-        gv[4] = QYY;
-        float w0, w1, w2;
-        wave_sum10(gv, w0, w1, w2);
-        if ((lane & 15) == 0) {  // one lane per row stores its row's totals
-          const int row = lane >> 4;
-          const int k = row == 1 ? 2 : (row == 2 ? 1 : row);
-          s_g[wv][j][k] = w0;  // this wavefront's own slots: plain stores
-          s_g[wv][j][4 + k] = w1;
-          if (!(row & 1)) s_g[wv][j][8 + (row >> 1)] = w2;
+#pragma unroll
+        for (int j = 0; j < GS; ++j) {
+          const float4 sq = s_q[jb + j];
+          const float2 mu = s_mu[jb + j];
+          dx[j] = fpx - mu.x;
+          dy0[j] = p[0].fpy - mu.y;
+          o[j] = sq.w;
+#pragma unroll
+          for (int i = 0; i < PPL; ++i) {
+            const float a = splat_alpha(dx[j], i == 0 ? dy0[j] : p[i].fpy - mu.y, sq.x, sq.y, sq.z, sq.w, G[j][i]);
+            act[j][i] = j < lim[i] && !(a < ru.amin);
+            hits |= __ballot(act[j][i]) != 0ull ? 1u << j : 0u;
+          }
+        }
+        hit |= uint64_t(hits) << jb;
+#pragma unroll
+        for (int j = GS - 1; j >= 0; --j) {
+          if (!((hits >> j) & 1u)) continue;
+          float u[PPL], c0 = 0.f, c1 = 0.f, c2 = 0.f, z = 0.f;
+#pragma unroll
+          for (int i = 0; i < PPL; ++i) {
+            float al, Gu;  // alpha, and dalpha/do = G (0 where clamped)
+            if (plain) {
+              Gu = act[j][i] ? G[j][i] : 0.f;
+              al = o[j] * Gu;
+            } else {
+              const float a = o[j] * G[j][i];
+              const bool below = a <= ru.amax;
+              al = act[j][i] ? (below ? a : ru.amax) : 0.f;
+              Gu = act[j][i] && below ? G[j][i] : 0.f;
+            }
+            const float iom = __builtin_amdgcn_rcpf(1.f - al);
+            p[i].T *= iom;
+            const float w = al * p[i].T;
+            const float D = S[j / 4][i][j % 4] - p[i].B;
+            p[i].B += al * D;
+            u[i] = (p[i].T * D + p[i].gATf * iom) * Gu;
+            c0 += p[i].gC0 * w;
+            c1 += p[i].gC1 * w;
+            c2 += p[i].gC2 * w;
+            z += p[i].gD * w;
+          }
+          // the lane's moments of u over y; its second pixel is one below the first (dy + 1)
+          const float dy = dy0[j];
+          float q = u[0], qy = dy * q, qyy = dy * qy;
+          if constexpr (PPL == 2) {
+            q = u[0] + u[1];
+            qy = dy * q + u[1];
+            qyy = dy * (qy + u[1]) + u[1];
+          }
+          // (each bank of four lanes holds one of the sums: they store the same word)
+          s_g[wv][jb + j][lane >> 2] = splat_sums(q, qy, qyy, c0, c1, c2, z, dx[j]);
         }
       }
+      if (lane == 0) s_hit[wv] = hit;
       __syncthreads();
-      flush_splat_sums<NT, NW, SB>(s_g, s_id, s_r0, s_r1, s_rgb, nstage, grad2d);
+      flush_splat_sums<NT, NW, SB>(s_g, s_hit, s_id, s_q, nstage, grad2d);
     }
   }
 }
@@ -2678,12 +2741,15 @@ hipError_t launch_first_nonfinite(const GaussDev& g, int sh_degree, uint32_t* fi
   return hipGetLastError();
 }
 
-// Persistent grid: blocks resident at once, at most `cap_per_cu` per compute unit (the
-// compositing kernels ran fastest below full occupancy: blend_fwd at 2 blocks per CU on
-// one 640x480 view, where its heaviest tiles' single-wavefront chains bound it and then
-// share a SIMD with fewer others, and at 4 with many tiles per CU (eight views);
-// blend_bwd at 5 (one pixel per lane) and 8 (two pixels per lane, blocks of half the
-// size), against more that fit).
+// Persistent grid: blocks resident at once, at most `cap_per_cu` per compute unit.  blend_fwd
+// runs fastest at 2 blocks per CU on one 640x480 view, where its heaviest tiles'
+// single-wavefront chains bound it and then share a SIMD with fewer others, and at 4 with
+// many tiles per CU (eight views).  blend_bwd: with many items the blocks in flight hide
+// each item's fixed latency and the more the better (tiles of 16, sixteen 1752x1168 views:
+// 18.5, 14.0, 12.7 ms at 5, 8, 10 per CU; eight uneven views 1204, 967, 930 us), while on one
+// 640x480 view 8 and 10 measure the same (128, 130 us).  Tiles of 8 hit the same few rows from
+// many blocks: 68, 80, 108 us at 5, 12, 24 per CU on 321x239 (1,230 tiles), 253, 249, 273 at 5,
+// 10, 20 on 640x480 (4,800), but 2800, 2809, 2597 over eight views (67k tiles).
 template <auto KERN>
 static int resident_blocks(int threads, int cap_per_cu) {
   static int per_cu = -1, cus = 1;  // one pair per kernel
@@ -2713,8 +2779,9 @@ static int device_cus() {
 constexpr int kFwdBlocksPerCU = 2;        // up to kFwdManyTilesPerCU tiles per CU
 constexpr int kFwdBlocksPerCUMany = 4;    // beyond
 constexpr int kFwdManyTilesPerCU = 16;
-constexpr int kBwdBlocksPerCU = 5;
-constexpr int kBwd2BlocksPerCU = 8;
+constexpr int kBwdBlocksPerCU = 5;        // tiles of 8 (one wavefront a block)
+constexpr int kBwdBlocksPerCUMany = 20;   // beyond 4 kFwdManyTilesPerCU tiles per CU
+constexpr int kBwd2BlocksPerCU = 10;      // tiles of 16 and 32
 constexpr int kBwdPixelsPerLane = 2;
 
 template <int TS, int BATCH>
@@ -2772,16 +2839,16 @@ hipError_t launch_loss_l1(const ViewTable& vt, float depth_w, float* part, float
   return hipGetLastError();
 }
 
-template <int TS, int BATCH>
+template <int TS>
 static void blend_bwd_t(const ViewTable& vt, const Rules& ru, const Records& rec, const uint2* ranges,
                         const uint32_t* vals, const float* T_final, const uint32_t* n_contrib, float* grad2d,
                         const TileQueue& q, const Ckpt& ck, hipStream_t s) {
   constexpr int PPL = TS >= 16 ? kBwdPixelsPerLane : 1;
-  constexpr int cap = TS >= 16 ? kBwd2BlocksPerCU : kBwdBlocksPerCU;
+  const int cap = TS >= 16 ? kBwd2BlocksPerCU
+                  : vt.total_tiles > 4 * kFwdManyTilesPerCU * device_cus() ? kBwdBlocksPerCUMany : kBwdBlocksPerCU;
   const int grid =
-      int(std::min<int64_t>(ck.cap_items, resident_blocks<k_blend_bwd2<TS, BATCH, PPL>>(TS * TS / PPL, cap)));
-  k_blend_bwd2<TS, BATCH, PPL><<<grid, TS * TS / PPL, 0, s>>>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d,
-                                                              q, ck);
+      int(std::min<int64_t>(ck.cap_items, resident_blocks<k_blend_bwd2<TS, PPL>>(TS * TS / PPL, cap)));
+  k_blend_bwd2<TS, PPL><<<grid, TS * TS / PPL, 0, s>>>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck);
 }
 
 hipError_t launch_blend_bwd(int tile, int batch, const ViewTable& vt, const Rules& ru, const Records& rec,
@@ -2790,14 +2857,10 @@ hipError_t launch_blend_bwd(int tile, int batch, const ViewTable& vt, const Rule
                             hipStream_t s, bool items_listed) {
   if (vt.total_tiles == 0) return hipSuccess;
   if (!items_listed) k_bwd_items<<<1, 1024, 0, s>>>(q.order, vt.total_tiles, ckpt_stride(batch), ck, q.ctrl);
-  const bool b256 = batch == 256;
   switch (tile) {
-    case 8: b256 ? blend_bwd_t<8, 256>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s)
-                 : blend_bwd_t<8, 128>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s); break;
-    case 32: b256 ? blend_bwd_t<32, 256>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s)
-                  : blend_bwd_t<32, 128>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s); break;
-    default: b256 ? blend_bwd_t<16, 256>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s)
-                  : blend_bwd_t<16, 128>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s); break;
+    case 8: blend_bwd_t<8>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s); break;
+    case 32: blend_bwd_t<32>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s); break;
+    default: blend_bwd_t<16>(vt, ru, rec, ranges, vals, T_final, n_contrib, grad2d, q, ck, s); break;
   }
   return hipGetLastError();
 }
