@@ -61,7 +61,7 @@ struct gsr_saved {
   int64_t cap_M = 0, cap_vis = 0;         // buffer capacities
   // depth sort and binning buffers
   uint32_t *dk = nullptr, *dv = nullptr, *dk2 = nullptr, *dv2 = nullptr;
-  uint32_t *hist = nullptr, *dtot = nullptr;
+  uint32_t *hist = nullptr, *dtot = nullptr, *vstart = nullptr;
   const uint32_t* order_hint = nullptr;  // per-tile work of a previous forward, or null
   BinPlan plan{};
   Ckpt ck{};                  // forward checkpoints and backward work items
@@ -306,14 +306,15 @@ gsr_status alloc_sort(gsr_saved* sv, int64_t cap_vis, int64_t cap_M, bool persis
   gsr_status st = GSR_OK;
   if ((st = alloc_in(sv, T, &sv->dk, cap_vis)) != GSR_OK || (st = alloc_in(sv, T, &sv->dv, cap_vis)) != GSR_OK ||
       (st = alloc_in(sv, T, &sv->dk2, cap_vis)) != GSR_OK || (st = alloc_in(sv, T, &sv->dv2, cap_vis)) != GSR_OK ||
-      (st = alloc_in(sv, T, &sv->hist, size_t(radix_hist_words(cap_vis)))) != GSR_OK ||
+      (st = alloc_in(sv, T, &sv->hist, size_t(radix_hist_words(cap_vis, sv->V)))) != GSR_OK ||
+      (st = alloc_in(sv, T, &sv->vstart, size_t(sv->V) + 1)) != GSR_OK ||
       (st = alloc_in(sv, T, &sv->dtot, 256)) != GSR_OK ||
       (st = alloc_in(sv, sv->blocks, &sv->vals, cap_M)) != GSR_OK ||
       (st = alloc_in(sv, T, &p.cnt1, size_t(n1))) != GSR_OK || (st = alloc_in(sv, T, &p.rowlist, cap_M)) != GSR_OK ||
       (st = alloc_in(sv, T, &p.rowinfo, size_t(p.rows))) != GSR_OK ||
       (st = alloc_in(sv, T, &p.seg_start, size_t(p.rows) + 1)) != GSR_OK ||
       (st = alloc_in(sv, T, &p.cntF, size_t(p.cap_flat))) != GSR_OK ||
-      (st = alloc_in(sv, T, &p.part, size_t(nparts))) != GSR_OK || (st = alloc_in(sv, T, &p.words, 4)) != GSR_OK)
+      (st = alloc_in(sv, T, &p.part, size_t(nparts))) != GSR_OK || (st = alloc_in(sv, T, &p.ord, kOrderWords)) != GSR_OK || (st = alloc_in(sv, T, &p.words, 4)) != GSR_OK)
     return st;
   return GSR_OK;
 }
@@ -416,12 +417,12 @@ hipError_t enqueue_sort_blend(gsr_saved* sv, hipStream_t s, bool timing) {
     bool alt = false;
     e = T(K_COMPACT, [&] {
       return launch_compact(sv->N, sv->V, sv->rec, sv->blocksums, sv->nblk, sv->d_total, sv->cap_M, sv->dk, sv->dv,
-                            sv->cap_vis, ovf, compact_scans(sv), s);
+                            sv->cap_vis, ovf, compact_scans(sv), sv->vstart, s);
     });
     if (e == hipSuccess)
       // depth keys are the bits of a positive binary32 depth: bit 31 is zero
-      e = launch_radix_sort(sv->dk, sv->dv, sv->dk2, sv->dv2, sv->hist, sv->dtot, sv->d_total + 1, sv->cap_vis, ovf,
-                            31, &alt, &sv->sort_passes, s, tm);
+      e = launch_radix_sort(sv->dk, sv->dv, sv->dk2, sv->dv2, sv->hist, sv->dtot, sv->vstart, sv->V, sv->d_total + 1,
+                            sv->cap_vis, ovf, 31, &alt, &sv->sort_passes, s, tm);
     if (alt) sorted = sv->dv2;
   }
   if (e == hipSuccess)

@@ -113,7 +113,14 @@ constexpr int kStepWords = 4;  // words 0..3 start at zero in every step (cleare
 constexpr int kOverflowSticky = 4;
 constexpr int kCtrlWords = 8;
 constexpr int kScanTile = 4096;  // elements per block of the device-wide scans
-constexpr int64_t kMaxBinCounts = int64_t(1) << 22;  // entries of each binning count array (soft)
+constexpr int kOrderBuckets = 257;  // work buckets of the tile order
+constexpr int kOrderWords = 2 * kOrderBuckets;
+constexpr int64_t kMaxBinCounts = int64_t(1) << 22;  // entries of the binning's (row, chunk) count array (soft)
+// entries of the (tile, segment) count array (soft).  It is sized by the pair capacity while the
+// row entries, some 5 to 15 times fewer, decide how many segments there are: with 2^22 a
+// 1752x1168 view of 70M pairs had 2,380 segments of 2,048 entries, hardly one for each block
+// that fits on the chip
+constexpr int64_t kMaxTileCounts = int64_t(1) << 24;
 
 // One camera plus where its tiles and pixels live in the concatenated spaces.
 struct ViewDev {
@@ -202,17 +209,17 @@ struct Ckpt {
 };
 
 // Two-level stable binning of the depth-sorted records into per-tile lists.
-//   rows:  the records are cut into chunks of 64 * rounds1; per (tile row, chunk) counts,
+//   rows:  the records are cut into chunks of 256 * rounds1; per (tile row, chunk) counts,
 //          scanned row-major, place every (record, row) entry of a chunk after those of
 //          earlier chunks, giving each tile row a depth-ordered list of (record, tx0..tx1)
-//   tiles: each row list is cut into segments of 64 * rounds2 entries; per (tile, segment)
+//   tiles: each row list is cut into segments of 256 * rounds2 entries; per (tile, segment)
 //          counts, flattened tile-major (row, column, segment) and scanned, place every
 //          (record, tile) pair; the scan is in global tile order, so it also gives the ranges
 struct BinPlan {
   int32_t rows;      // tile rows over all views
   int32_t nch1;      // chunks of the depth-sorted records
-  int32_t rounds1;   // 64-record rounds per chunk
-  int32_t rounds2;   // 64-entry rounds per segment
+  int32_t rounds1;   // 256-record rounds per chunk
+  int32_t rounds2;   // 256-entry rounds per segment
   int64_t cap_M;     // capacity of row entries and of pairs
   int64_t cap_seg;   // capacity of segments
   int64_t cap_flat;  // capacity of flat (tile, segment) counts
@@ -222,6 +229,7 @@ struct BinPlan {
   uint32_t* seg_start;   // [rows + 1] first segment of each row
   uint32_t* cntF;        // flat (tile, segment) counts, then exclusive offsets
   uint32_t* part;        // partial sums of the device-wide scans
+  uint32_t* ord;         // [kOrderWords] bucket counters and cursors of the tile order, zero at a step's start
   unsigned long long* words;  // [0] row entries, [1] segments, [2] flat size, [3] pairs placed
 };
 
@@ -285,24 +293,25 @@ hipError_t launch_project(int deg, const GaussDev& g, const ViewTable& vt, const
 hipError_t launch_scan_pairs(uint2* blocksums, int count, unsigned long long* totals, hipStream_t s);
 // raw: blocksums as the projection wrote them (not scanned; at most kCompactRawMax of
 // them), and the compaction writes totals[0..1] itself; else scanned by launch_scan_pairs,
-// which wrote the totals.
+// which wrote the totals.  vstart gets views + 1 words: where each view's records start.
 constexpr int64_t kCompactRawMax = 4096;
 hipError_t launch_compact(int64_t n, int views, const Records& rec, const uint2* blocksums, int nblk,
                           unsigned long long* totals, int64_t cap_M, uint32_t* dkeys, uint32_t* dvals,
-                          int64_t cap, uint32_t* overflow, bool raw, hipStream_t s);
+                          int64_t cap, uint32_t* overflow, bool raw, uint32_t* vstart, hipStream_t s);
 // Checkpoint stride and checkpoints per tile, and the backward work items of all tiles,
 // at a batch size.
 int ckpt_stride(int batch);
 int ckpt_per_tile(int batch);
 int64_t bwd_items_cap(int total_tiles, int batch);
 // Stable LSD radix sort of min(*count, cap) (key, value) pairs by their key_bits low bits
-// (at most 32; 8-bit passes); the result is in the _alt arrays when *result_in_alt.  hist
-// holds radix_hist_words(cap) words, digit_tot 256.
-int radix_hist_words(int64_t cap);
+// (at most 32; 8-bit passes), each view's keys (places vstart[v] .. vstart[v + 1], device) by
+// themselves; the result is in the _alt arrays when *result_in_alt.  hist holds
+// radix_hist_words(cap, views) words, digit_tot 256.
+int64_t radix_hist_words(int64_t cap, int views);
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                             uint32_t* hist, uint32_t* digit_tot, const unsigned long long* count, int64_t cap,
-                             const uint32_t* overflow, int key_bits, bool* result_in_alt, int* passes, hipStream_t s,
-                             Timer* tm);
+                             uint32_t* hist, uint32_t* digit_tot, const uint32_t* vstart, int views,
+                             const unsigned long long* count, int64_t cap, const uint32_t* overflow, int key_bits,
+                             bool* result_in_alt, int* passes, hipStream_t s, Timer* tm);
 // Sizes of a binning plan for capacities (cap_vis, cap_M); pointers are left null.
 BinPlan bin_plan(const ViewTable& vt, int64_t cap_vis, int64_t cap_M);
 // exact_k > 0: per tile row only the columns the ellipse d^T Q d <= exact_k^2 reaches.

@@ -77,57 +77,9 @@ __device__ __forceinline__ f32x4 mfma_rank1(float a, float b, f32x4 c, int u) {
   }
 }
 
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, 0xF, 0xF, false));
-}
-
-// Minimum over the wavefront, returned as a wavefront-uniform value: each 16-lane row is
-// reduced with DPP (quad swaps, half-row and row mirrors), then the four row results are
-// read from lanes 0, 16, 32 and 48.  Needs every lane active.
-__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-  v = min(v, dpp_u32<0xB1>(v));
-  v = min(v, dpp_u32<0x4E>(v));
-  v = min(v, dpp_u32<0x141>(v));
-  v = min(v, dpp_u32<0x140>(v));
-  const uint32_t a = uint32_t(__builtin_amdgcn_readlane(int(v), 0));
-  const uint32_t b = uint32_t(__builtin_amdgcn_readlane(int(v), 16));
-  const uint32_t c = uint32_t(__builtin_amdgcn_readlane(int(v), 32));
-  const uint32_t d = uint32_t(__builtin_amdgcn_readlane(int(v), 48));
-  return min(min(a, b), min(c, d));
-}
-
-// A VALU copy of v.  Registers read by readlane inside a loop that also stores to
-// global memory are copied once after their load, so the loop does not wait for its own
-// stores (memory counter) before each readlane.
-__device__ __forceinline__ uint32_t valu_copy(uint32_t v) {
-  uint32_t r;
-  asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
-  return r;
-}
-
 __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   for (int off = 32; off > 0; off >>= 1) v = max(v, uint32_t(__shfl_xor(v, off)));
   return v;
-}
-
-// Maximum over the wavefront as a wavefront-uniform value, by the DPP steps of
-// wave_min_u32.  Needs every lane active.
-__device__ __forceinline__ uint32_t wave_max_uniform_u32(uint32_t v) {
-  v = max(v, dpp_u32<0xB1>(v));
-  v = max(v, dpp_u32<0x4E>(v));
-  v = max(v, dpp_u32<0x141>(v));
-  v = max(v, dpp_u32<0x140>(v));
-  const uint32_t a = uint32_t(__builtin_amdgcn_readlane(int(v), 0));
-  const uint32_t b = uint32_t(__builtin_amdgcn_readlane(int(v), 16));
-  const uint32_t c = uint32_t(__builtin_amdgcn_readlane(int(v), 32));
-  const uint32_t d = uint32_t(__builtin_amdgcn_readlane(int(v), 48));
-  return uint32_t(__builtin_amdgcn_readfirstlane(int(max(max(a, b), max(c, d)))));
-}
-
-// base + the number of lanes below this one set in m (v_mbcnt)
-__device__ __forceinline__ uint32_t rank_below(uint64_t m, uint32_t base) {
-  return __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), base));
 }
 
 __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
@@ -702,11 +654,12 @@ __device__ __forceinline__ uint32_t clamp_count(const unsigned long long* count,
 // raw: the block sums are the projection's, not scanned (at most kCompactRawMax of them):
 // each block adds the visible records of the blocks in front of it itself, and the last
 // block writes the totals (pairs, visible records) to totals[0..1].  Otherwise they were
-// scanned (k_scan_pairs, which wrote the totals).
+// scanned (k_scan_pairs, which wrote the totals).  vstart[0 .. views]: where each view's
+// records start, and their end.
 __global__ __launch_bounds__(kProjThreads) void k_compact(int64_t n, Records rec, const uint2* blocksums, int nblk,
                                                           unsigned long long* totals, int64_t cap_M,
                                                           uint32_t* dkeys, uint32_t* dvals, int64_t cap,
-                                                          uint32_t* overflow, int raw) {
+                                                          uint32_t* overflow, int raw, uint32_t* vstart) {
   __shared__ uint32_t red[kProjThreads / 64];
   __shared__ unsigned long long red64[kProjThreads / 64];
   const int v = blockIdx.y;
@@ -740,7 +693,9 @@ __global__ __launch_bounds__(kProjThreads) void k_compact(int64_t n, Records rec
     // reads the flag (every later kernel then sees zero records)
     if (me == 0 && threadIdx.x == 0 && totals[0] > (unsigned long long)cap_M) raise_overflow(overflow);
   }
+  if (blockIdx.x == 0 && threadIdx.x == 0) vstart[v] = base;  // the view's first place
   const uint32_t excl = block_exclusive_scan_u32(vis, red);
+  if (me == nb - 1 && threadIdx.x == kProjThreads - 1) vstart[gridDim.y] = base + excl + vis;
   if (!vis) return;
   const uint32_t off = base + excl;
   if (int64_t(off) >= cap) {
@@ -752,13 +707,18 @@ __global__ __launch_bounds__(kProjThreads) void k_compact(int64_t n, Records rec
 }
 
 // ------------------------------------------------------------------------------------
-// K4: stable LSD radix sort of (u32 key, u32 value) by digits of BITS bits, count read
-// from the device (clamped to the capacity the grid was sized for).  Per pass:
-//   hist:    per-block digit histograms, stored digit-major [2^BITS][nblk]
-//   rowscan: one block per digit scans its row -> start of each block in that digit,
+// K4: stable LSD radix sort of (u32 key, u32 value) by digits of BITS bits, each view's
+// keys by themselves (the compaction leaves them in view order, and a tile's list needs no
+// order between views; records in view order let the binning handle one view's tile rows at
+// a time).  A key tile is kSortTile keys of one view; counts are read from the device
+// (clamped to the capacity the grid was sized for).  Per pass:
+//   hist:    per-tile digit histograms, stored digit-major [2^BITS][ntile]
+//   rowscan: one block per digit scans its row -> keys of the digit in front of each tile,
 //            and the digit total
 //   scatter: each block ranks its keys stably (wavefront multisplit by ballots, then
-//            across the four wavefronts through LDS) and writes them to their slots
+//            across the four wavefronts through LDS) and writes them to their slots: the
+//            view's start, its keys of smaller digits and the row's count since the view's
+//            first tile
 // ------------------------------------------------------------------------------------
 // 8-bit digits: wider ones (11 bits, three passes for a depth key) ran slower on MI355X,
 // their digit-major histograms being written and read across many more cache lines
@@ -773,10 +733,34 @@ __device__ __forceinline__ int xcd_block(int b, int G) { return (b & 7) * (G >> 
 static int xcd_grid(int64_t blocks) { return int((blocks + 7) / 8 * 8); }
 
 
+// The keys of tile tb: its view's first key and end (in the key arrays), this tile's first key, the view's
+// first tile and the next view's (ntile: past the last).  False past the last tile.
+struct SortTile {
+  uint32_t vbeg, vend, beg;
+  int t0, t1;
+};
+__device__ __forceinline__ bool sort_tile(const uint32_t* vstart, int views, const unsigned long long* count, int64_t cap,
+                                          const uint32_t* overflow, int tb, SortTile& o) {
+  const uint32_t M = clamp_count(count, cap, overflow);
+  o.t1 = 0;
+  for (int v = 0; v < views; ++v) {
+    o.vbeg = min(vstart[v], M);
+    o.vend = min(vstart[v + 1], M);
+    o.t0 = o.t1;
+    o.t1 += int((o.vend - o.vbeg + kSortTile - 1) / kSortTile);
+    if (tb < o.t1) {
+      o.beg = o.vbeg + uint32_t(tb - o.t0) * kSortTile;
+      return true;
+    }
+  }
+  return false;
+}
+
 template <int BITS>
-__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint32_t* keys, const unsigned long long* count,
-                                                             int64_t cap, const uint32_t* overflow, int shift,
-                                                             uint32_t* hist, int nblk) {
+__global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint32_t* keys, const uint32_t* vstart, int views,
+                                                             const unsigned long long* count, int64_t cap,
+                                                             const uint32_t* overflow, int shift, uint32_t* hist,
+                                                             int nblk) {
   constexpr int D = 1 << BITS;
   constexpr uint32_t MASK = D - 1;
   __shared__ uint32_t h[D];
@@ -784,12 +768,13 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint32_t* key
   if (tb >= nblk) return;                            // block-uniform
   for (int d = threadIdx.x; d < D; d += kSortThreads) h[d] = 0;
   __syncthreads();
-  const int64_t M = clamp_count(count, cap, overflow);
-  const int64_t base = int64_t(tb) * kSortTile;
+  SortTile st;
+  if (sort_tile(vstart, views, count, cap, overflow, tb, st)) {
 #pragma unroll 4
-  for (int i = 0; i < kSortItems; ++i) {
-    const int64_t idx = base + i * kSortThreads + threadIdx.x;
-    if (idx < M) atomicAdd(&h[(keys[idx] >> shift) & MASK], 1u);
+    for (int i = 0; i < kSortItems; ++i) {
+      const uint32_t idx = st.beg + uint32_t(i * kSortThreads) + threadIdx.x;
+      if (idx < st.vend) atomicAdd(&h[(keys[idx] >> shift) & MASK], 1u);
+    }
   }
   __syncthreads();
   for (int d = threadIdx.x; d < D; d += kSortThreads) hist[int64_t(d) * nblk + tb] = h[d];
@@ -817,6 +802,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_rowscan(uint32_t* hist, 
 template <int BITS>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t* kin, const uint32_t* vin,
                                                                 uint32_t* kout, uint32_t* vout,
+                                                                const uint32_t* vstart, int views,
                                                                 const unsigned long long* count, int64_t cap,
                                                                 const uint32_t* overflow, int shift,
                                                                 const uint32_t* hist, const uint32_t* digit_tot,
@@ -834,20 +820,24 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t* 
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int tb = xcd_block(blockIdx.x, gridDim.x);  // this block's tile of keys
   if (tb >= nblk) return;                            // block-uniform
-  const int64_t M = clamp_count(count, cap, overflow);
-  // first slot of each digit: thread t scans digits t * DPT .. t * DPT + DPT - 1
+  SortTile st;
+  if (!sort_tile(vstart, views, count, cap, overflow, tb, st)) return;  // block-uniform
+  // first slot of each digit: thread t scans the view's digits t * DPT .. t * DPT + DPT - 1
   {
-    uint32_t tot[DPT], sum = 0;
-#pragma unroll
-    for (int j = 0; j < DPT; ++j) {
-      tot[j] = digit_tot[t * DPT + j];
-      sum += tot[j];
-    }
-    uint32_t run = block_exclusive_scan_u32(sum, red);
+    uint32_t tot[DPT], at[DPT], sum = 0;
 #pragma unroll
     for (int j = 0; j < DPT; ++j) {
       const int d = t * DPT + j;
-      base[0][d] = run + hist[int64_t(d) * nblk + tb];
+      const uint32_t* row = hist + int64_t(d) * nblk;
+      const uint32_t first = row[st.t0];
+      tot[j] = (st.t1 < nblk ? row[st.t1] : digit_tot[d]) - first;
+      at[j] = row[tb] - first;
+      sum += tot[j];
+    }
+    uint32_t run = st.vbeg + block_exclusive_scan_u32(sum, red);
+#pragma unroll
+    for (int j = 0; j < DPT; ++j) {
+      base[0][t * DPT + j] = run + at[j];
       run += tot[j];
     }
   }
@@ -860,22 +850,20 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t* 
       wcnt[1][i][t + kSortThreads * j] = 0;
     }
   __syncthreads();
-  const int64_t b0 = int64_t(tb) * kSortTile;
   const uint64_t lt_mask = (1ull << lane) - 1ull;
   // every round's key and value loaded up front (one memory latency per block, not one
   // per round)
   uint32_t kk[kSortItems], vv[kSortItems];
 #pragma unroll
   for (int r = 0; r < kSortItems; ++r) {
-    const int64_t idx = b0 + r * kSortThreads + t;
-    kk[r] = idx < M ? kin[idx] : 0u;
-    vv[r] = idx < M ? vin[idx] : 0u;
+    const uint32_t idx = st.beg + uint32_t(r * kSortThreads + t);
+    kk[r] = idx < st.vend ? kin[idx] : 0u;
+    vv[r] = idx < st.vend ? vin[idx] : 0u;
   }
 #pragma unroll
   for (int r = 0; r < kSortItems; ++r) {
     const int b = r & 1;
-    const int64_t idx = b0 + r * kSortThreads + t;
-    const bool valid = idx < M;
+    const bool valid = st.beg + uint32_t(r * kSortThreads + t) < st.vend;
     const uint32_t key = kk[r], val = vv[r];
     const uint32_t d = valid ? (key >> shift) & MASK : 0u;
     uint64_t peers = __ballot(valid);
@@ -994,11 +982,144 @@ __global__ __launch_bounds__(256) void k_scan_down(uint32_t* a, int64_t cap, con
 // ------------------------------------------------------------------------------------
 // K3/K4 binning (see BinPlan).  Both stages place items that cover a contiguous run of
 // bins [lo, hi] (tile rows of a record, tile columns of a row entry) stably: chunk by
-// chunk from scanned per-(bin, chunk) counts, and inside a chunk by one wavefront that
-// walks its 64 items' bins in ascending order; for each bin the covering lanes take
-// consecutive slots in lane order from the bin's next free slot, kept in LDS (loaded from
-// the scanned counts when the chunk starts).
+// chunk from scanned per-(bin, chunk) counts, and inside a chunk by one block, 256 items
+// a round (place_round).
+//
+// A round's pairs are written densely.  Each wavefront's 64 items become one 64-bit
+// coverage mask per bin (a run as two flipped bits, at lo and past hi, and an XOR scan over
+// the bins); population counts give every bin's pairs and a scan their places in bin order.
+// The lanes then take a bin each and list its items into LDS (as many steps as the fullest
+// bin has items), and consecutive lanes write out consecutive pairs: a bin's pairs of the
+// round are one contiguous run of the output.  (One bin a step for a wavefront's 64 items, the
+// covering lanes storing directly, left most lanes of a store idle; and with the records of
+// sixteen views interleaved every wavefront walked the rows of all of them.)
+//
+// Kernel trace, rows + tiles stage, that walk against this: 25 + 16 -> 23 + 16 us (640x480,
+// 500k), 30 + 351 -> 23 + 168 us (1752x1168, 70M pairs), 395 + 368 -> 140 + 183 us (eight uneven
+// views), 4193 + 1934 -> 867 + 783 us (sixteen 1752x1168 views).  It is bound by VALU issue
+// (87 of 168 us) and by the rounds' barriers.
 // ------------------------------------------------------------------------------------
+constexpr int kPlaceThreads = 256;  // items of a round
+constexpr int kPlaceBins = 256;     // bins handled at once (more: window after window)
+constexpr int kPlaceStage = 4096;   // pairs listed at once
+
+// The block's LDS, sized for the bins of a launch (place_lds bytes of dynamic LDS): a short one
+// lets more blocks share a CU.
+struct PlaceLds {
+  uint64_t* mask;   // [4][bins + 1] per wavefront and bin, the items that cover it
+  uint32_t* next;   // [bins] each bin's next free slot
+  uint32_t* pre;    // [bins] the round's pairs in front of each bin
+  uint32_t* woff;   // [bins] within a bin, the pairs of wavefronts 0, 0-1, 0-2 (8 bits each, from bit 8)
+  uint32_t* delta;  // [bins] next - pre
+  uint16_t* stage;  // [kPlaceStage] (bin << 8) | item
+  uint32_t* red;    // [5]: block sums, the round's pairs
+  int bins;
+};
+static size_t place_lds(int bins) { return size_t(bins + 1) * 32 + size_t(bins) * 16 + kPlaceStage * 2 + 32; }
+__device__ __forceinline__ PlaceLds place_carve(unsigned char* base, int bins) {
+  PlaceLds L;
+  L.bins = bins;
+  L.mask = reinterpret_cast<uint64_t*>(base);
+  L.next = reinterpret_cast<uint32_t*>(base + size_t(bins + 1) * 32);
+  L.pre = L.next + bins;
+  L.woff = L.pre + bins;
+  L.delta = L.woff + bins;
+  L.red = L.delta + bins;
+  L.stage = reinterpret_cast<uint16_t*>(L.red + 8);
+  return L;
+}
+
+// Inclusive XOR scan over the wavefront (DPP row shifts, then the rows' totals broadcast to
+// the rows behind).  Needs every lane active.
+__device__ __forceinline__ uint32_t wave_xor_scan(uint32_t v) {
+#define GSR_XOR_STEP(CTRL, ROWS) \
+  v ^= uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, ROWS, 0xF, false))
+  GSR_XOR_STEP(0x111, 0xF);  // row_shr:1
+  GSR_XOR_STEP(0x112, 0xF);
+  GSR_XOR_STEP(0x114, 0xF);
+  GSR_XOR_STEP(0x118, 0xF);
+  GSR_XOR_STEP(0x142, 0xA);  // row_bcast:15
+  GSR_XOR_STEP(0x143, 0xC);  // row_bcast:31
+#undef GSR_XOR_STEP
+  return v;
+}
+
+// Lists a wavefront's pairs of one window: lane x's bin, its items in order from place pos
+// (CHECK: only places below kPlaceStage).  One item of every lane's bin a step.
+template <bool CHECK>
+__device__ __forceinline__ void list_items(uint16_t* stage, uint32_t m, uint32_t& pos, uint32_t code) {
+  while (m) {
+    if (!CHECK || pos < uint32_t(kPlaceStage)) stage[pos] = uint16_t(code + uint32_t(__builtin_ctz(m)));
+    ++pos;
+    m &= m - 1u;
+  }
+}
+
+// One round: this thread's item covers bins [lo, hi] of nb <= L.bins (lo > hi: none); emit(slot,
+// item, bin) writes a pair.  Called by all 256 threads; L.next must be ready (a barrier
+// after it was written) and is advanced; ends with a barrier.
+template <class Emit>
+__device__ __forceinline__ void place_round(const PlaceLds& L, int nb, int lo, int hi, Emit&& emit) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const int stride = L.bins + 1;
+  uint64_t* mask = L.mask + w * stride;
+  for (int x = lane; x <= nb; x += 64) mask[x] = 0ull;
+  __builtin_amdgcn_wave_barrier();
+  if (lo <= hi) {
+    atomicXor(reinterpret_cast<unsigned long long*>(&mask[lo]), 1ull << lane);
+    atomicXor(reinterpret_cast<unsigned long long*>(&mask[hi + 1]), 1ull << lane);
+  }
+  __builtin_amdgcn_wave_barrier();
+  uint64_t carry = 0;
+  for (int x0 = 0; x0 < nb; x0 += 64) {
+    const uint64_t v = x0 + lane < nb ? mask[x0 + lane] : 0ull;
+    const uint32_t l = wave_xor_scan(uint32_t(v)), h = wave_xor_scan(uint32_t(v >> 32));
+    const uint64_t m = ((uint64_t(h) << 32) | l) ^ carry;
+    if (x0 + lane < nb) mask[x0 + lane] = m;
+    carry ^= (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(h), 63))) << 32) |
+             uint32_t(__builtin_amdgcn_readlane(int(l), 63));
+  }
+  __syncthreads();
+  uint32_t tot = 0;
+  if (t < nb) {
+    const uint32_t c0 = __popcll(L.mask[t]), c1 = __popcll(L.mask[stride + t]), c2 = __popcll(L.mask[2 * stride + t]);
+    tot = c0 + c1 + c2 + __popcll(L.mask[3 * stride + t]);
+    L.woff[t] = (c0 << 8) | ((c0 + c1) << 16) | ((c0 + c1 + c2) << 24);
+  }
+  const uint32_t ex = block_exclusive_scan_u32(tot, L.red);
+  if (t < nb) {
+    const uint32_t nx = L.next[t];
+    L.pre[t] = ex;
+    L.delta[t] = nx - ex;
+    L.next[t] = nx + tot;
+  }
+  if (t == kPlaceThreads - 1) L.red[4] = ex + tot;
+  __syncthreads();
+  const uint32_t total = L.red[4];
+  for (uint32_t p0 = 0; p0 < total; p0 += kPlaceStage) {
+    for (int x = lane; x < nb; x += 64) {
+      const uint64_t m = mask[x];
+      uint32_t pos = L.pre[x] + (w == 0 ? 0u : (L.woff[x] >> (8 * w)) & 255u) - p0;  // (wraps in front of p0)
+      const uint32_t code = (uint32_t(x) << 8) | uint32_t(64 * w);
+      if (total <= uint32_t(kPlaceStage)) {
+        list_items<false>(L.stage, uint32_t(m), pos, code);
+        list_items<false>(L.stage, uint32_t(m >> 32), pos, code + 32u);
+      } else {
+        list_items<true>(L.stage, uint32_t(m), pos, code);
+        list_items<true>(L.stage, uint32_t(m >> 32), pos, code + 32u);
+      }
+    }
+    __syncthreads();
+    const uint32_t n = min(total - p0, uint32_t(kPlaceStage));
+    for (uint32_t i = t; i < n; i += kPlaceThreads) {
+      const uint32_t code = L.stage[i];
+      const uint32_t x = code >> 8;
+      emit(L.delta[x] + p0 + i, int(code & 255u), int(x));
+    }
+    __syncthreads();
+  }
+}
+
 __device__ __forceinline__ int view_of_tile(const ViewTable& vt, int tile) {
   int v = 0;
   for (int i = 1; i < vt.nviews; ++i)
@@ -1017,20 +1138,7 @@ __device__ __forceinline__ uint32_t view_of_record(const ViewTable& vt, uint32_t
   return vt.nviews == 1 ? 0u : rid / uint32_t(n);
 }
 
-// The column run of a row entry: for (record, rect columns) `entry` in its k-th tile row,
-// with exact tiles the run the projection kept (rr, loaded by load_row_runs before the
-// row walk) for k < kRowRuns and past those rows the rectangle's columns marked kRunUncut,
-// so that stage 2 cuts them; without exact tiles the rectangle's columns.
-__device__ __forceinline__ uint32_t row_entry_run(const Records& rec, uint2 entry, const uint32_t (&rr)[kRowRuns],
-                                                  uint32_t k) {
-  if (!rec.runs) return entry.y;
-  uint32_t r = entry.y | kRunUncut;
-#pragma unroll
-  for (int j = 0; j < kRowRuns; ++j)
-    if (k == uint32_t(j)) r = rr[j];
-  return r;
-}
-
+// The column runs that the projection kept for a record's first kRowRuns tile rows (exact tiles).
 __device__ __forceinline__ void load_row_runs(const Records& rec, uint2 entry, bool valid, uint32_t (&rr)[kRowRuns]) {
 #pragma unroll
   for (int j = 0; j < kRowRuns; ++j) rr[j] = 0u;
@@ -1056,9 +1164,11 @@ __global__ __launch_bounds__(256) void k_bin_rows_count(ViewTable vt, int64_t n,
   if (chunk >= plan.nch1) return;  // block-uniform
   for (int i = threadIdx.x; i < R; i += 256) hist[i] = 0;
   __syncthreads();
+  if (chunk == 0)  // the tile order's counters (see tile_order_count)
+    for (int i = threadIdx.x; i < kOrderWords; i += 256) plan.ord[i] = 0u;
   const int64_t NV = clamp_count(nvis, cap_vis, overflow);
-  const int64_t beg = int64_t(chunk) * 64 * plan.rounds1;
-  const int64_t end = min(NV, beg + int64_t(64) * plan.rounds1);
+  const int64_t beg = int64_t(chunk) * kPlaceThreads * plan.rounds1;
+  const int64_t end = min(NV, beg + int64_t(kPlaceThreads) * plan.rounds1);
   for (int64_t i = beg + threadIdx.x; i < end; i += 256) {
     const uint32_t rid = dvals[i];
     const uint2 rc = rec.rect[rid];
@@ -1079,7 +1189,7 @@ __device__ void rows_meta(const ViewTable& vt, const BinPlan& plan, uint32_t* ov
   const int per = (R + NT - 1) / NT;
   const int beg = min(R, t * per), end = min(R, beg + per);
   const unsigned long long E1 = plan.words[0];
-  const uint32_t S2 = 64u * uint32_t(plan.rounds2);
+  const uint32_t S2 = uint32_t(kPlaceThreads) * uint32_t(plan.rounds2);
   auto row = [&](int r, uint32_t& start, uint32_t& len, uint32_t& nseg, uint32_t& w) {
     start = plan.cnt1[int64_t(r) * plan.nch1];
     const unsigned long long next = r + 1 < R ? plan.cnt1[int64_t(r + 1) * plan.nch1] : E1;
@@ -1115,164 +1225,67 @@ __device__ void rows_meta(const ViewTable& vt, const BinPlan& plan, uint32_t* ov
   }
 }
 
-// stage 1 placement: one wavefront per chunk writes (record, column run) entries into the
-// row lists
-__global__ __launch_bounds__(64) void k_bin_rows_scatter(ViewTable vt, int64_t n, Records rec, const uint32_t* dvals,
-                                                         const unsigned long long* nvis, int64_t cap_vis,
-                                                         uint32_t* overflow, BinPlan plan) {
-  extern __shared__ uint32_t next[];  // next free slot of each row for this chunk
-  __shared__ unsigned long long s_part[64];
-  if (blockIdx.x == gridDim.x - 1) rows_meta<64>(vt, plan, overflow, s_part);
-  const int R = plan.rows;
-  const int lane = threadIdx.x;
+// stage 1 placement: one block per chunk writes (record, column run) entries into the row
+// lists.  With exact tiles an entry carries the run that the projection kept for the k-th tile
+// row of its record (k < kRowRuns), and past those rows the rectangle's columns marked
+// kRunUncut, so that stage 2 cuts them; without exact tiles the rectangle's columns.
+__global__ __launch_bounds__(kPlaceThreads) void k_bin_rows_place(ViewTable vt, int64_t n, Records rec,
+                                                                  const uint32_t* dvals,
+                                                                  const unsigned long long* nvis, int64_t cap_vis,
+                                                                  uint32_t* overflow, BinPlan plan) {
+  extern __shared__ __align__(16) unsigned char s_dyn[];  // place_lds(bins) bytes, bins = min(rows, kPlaceBins)
+  __shared__ uint32_t s_rr[kRowRuns + 1][kPlaceThreads];  // the round's row runs, row k of item j at [k][j]
+  __shared__ uint32_t s_rid[kPlaceThreads], s_first[kPlaceThreads];
+  static_assert(sizeof(s_rr) >= kPlaceThreads * sizeof(unsigned long long), "s_rr serves rows_meta first");
+  const int t = threadIdx.x, R = plan.rows;
+  const PlaceLds L = place_carve(s_dyn, min(R, kPlaceBins));
+  if (blockIdx.x == gridDim.x - 1)
+    rows_meta<kPlaceThreads>(vt, plan, overflow, reinterpret_cast<unsigned long long*>(&s_rr[0][0]));
+  const int chunk = xcd_block(blockIdx.x, gridDim.x);
   const int64_t NV = clamp_count(nvis, cap_vis, overflow);
-  const int64_t beg = int64_t(blockIdx.x) * 64 * plan.rounds1;
-  if (beg >= NV) return;
-  for (int i = lane; i < R; i += 64) next[i] = plan.cnt1[int64_t(i) * plan.nch1 + blockIdx.x];
-  __syncthreads();
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
-  for (int r = 0; r < plan.rounds1; ++r) {
-    const int64_t r0 = beg + int64_t(r) * 64;
-    if (r0 >= NV) break;
-    const int64_t i = r0 + lane;
-    uint32_t cur = 0xFFFFFFFFu, hi = 0u;
-    uint2 entry = make_uint2(0u, 0u);
-    if (i < NV) {
-      const uint32_t rid = dvals[i];
-      const uint2 rc = rec.rect[rid];
-      const int ro = vt.v[view_of_record(vt, rid, n)].row_off;
-      cur = uint32_t(ro) + (rc.y & 0xFFFFu);
-      hi = min(uint32_t(ro) + (rc.y >> 16), uint32_t(R - 1));
-      entry = make_uint2(rid, rc.x);
-    }
-    const uint32_t first = cur;
-    uint32_t rr[kRowRuns];
-    load_row_runs(rec, entry, cur != 0xFFFFFFFFu, rr);
-    for (uint32_t y = wave_min_u32(cur); y != 0xFFFFFFFFu; y = wave_min_u32(cur)) {
-      const bool on = cur == y;
-      const uint64_t m = __ballot(on);
-      const uint32_t base = next[y];
-      if (on) {
-        const uint32_t dst = base + uint32_t(__popcll(m & lt_mask));
-        if (int64_t(dst) < plan.cap_M) plan.rowlist[dst] = make_uint2(entry.x, row_entry_run(rec, entry, rr, y - first));
-        cur = cur < hi ? cur + 1u : 0xFFFFFFFFu;
+  const int64_t beg = int64_t(chunk) * kPlaceThreads * plan.rounds1;
+  if (chunk >= plan.nch1 || beg >= NV) return;  // block-uniform
+  // the records are in view order: the chunk's rows are those of its first to its last record's view
+  const int64_t end = min(NV, beg + int64_t(kPlaceThreads) * plan.rounds1);
+  const ViewDev& v0 = vt.v[view_of_record(vt, dvals[beg], n)];
+  const ViewDev& v1 = vt.v[view_of_record(vt, dvals[end - 1], n)];
+  const int y0 = v0.row_off, y1 = min(v1.row_off + v1.tiles_y, R);
+  for (int w0 = y0; w0 < y1; w0 += kPlaceBins) {
+    const int nb = min(kPlaceBins, y1 - w0);
+    __syncthreads();
+    if (t < nb) L.next[t] = plan.cnt1[int64_t(w0 + t) * plan.nch1 + chunk];
+    for (int r = 0; r < plan.rounds1; ++r) {
+      const int64_t i = beg + int64_t(r) * kPlaceThreads + t;
+      if (i - t >= end) break;  // block-uniform
+      int lo = 1, hi = 0;
+      uint2 entry = make_uint2(0u, 0u);
+      uint32_t first = 0;
+      if (i < end) {
+        const uint32_t rid = dvals[i];
+        const uint2 rc = rec.rect[rid];
+        const int ro = vt.v[view_of_record(vt, rid, n)].row_off;
+        lo = ro + int(rc.y & 0xFFFFu);
+        hi = min(ro + int(rc.y >> 16), R - 1);
+        first = uint32_t(lo);
+        entry = make_uint2(rid, rc.x);
+        lo = max(lo, w0) - w0;
+        hi = min(hi, w0 + nb - 1) - w0;
       }
-      if (lane == 0) next[y] = base + uint32_t(__popcll(m));
-    }
-  }
-}
-
-// Next free slot of bin b when the slots of bins lane + 64 k sit in register k of that
-// lane: readlanes and selects only, so the walks over bins carry no branches.
-template <int NREG>
-__device__ __forceinline__ uint32_t slot_of(const uint32_t (&nx)[NREG], uint32_t b) {
-  const int src = int(b & 63u), kb = int(b >> 6);
-  uint32_t base = uint32_t(__builtin_amdgcn_readlane(int(nx[0]), src));
+      if (__syncthreads_or(lo <= hi) == 0) continue;
+      if (rec.runs) {
+        uint32_t rr[kRowRuns];
+        load_row_runs(rec, entry, lo <= hi, rr);
 #pragma unroll
-  for (int k = 1; k < NREG; ++k) {
-    const uint32_t v = uint32_t(__builtin_amdgcn_readlane(int(nx[k]), src));
-    base = kb == k ? v : base;
-  }
-  return base;
-}
-
-// Advances every bin's next free slot (bin lane + 64 k in register k) by the number of
-// this round's lanes whose run [lo, hi] covers it (lo = 0xFFFFFFFF: no run), from a
-// difference histogram in the wavefront's LDS words diff[0 .. 64 NREG] (+1 at lo, -1
-// past hi) and its inclusive scan over the bins.
-template <int NREG>
-__device__ __forceinline__ void advance_slots(uint32_t (&nx)[NREG], uint32_t* diff, uint32_t lo, uint32_t hi,
-                                              int lane) {
-#pragma unroll
-  for (int k = 0; k < NREG; ++k) diff[lane + 64 * k] = 0u;
-  if (lane == 0) diff[64 * NREG] = 0u;
-  __builtin_amdgcn_wave_barrier();
-  if (lo != 0xFFFFFFFFu) {
-    atomicAdd(&diff[lo], 1u);
-    atomicAdd(&diff[hi + 1u], 0xFFFFFFFFu);
-  }
-  __builtin_amdgcn_wave_barrier();
-  uint32_t carry = 0;
-#pragma unroll
-  for (int k = 0; k < NREG; ++k) {
-    uint32_t v = diff[lane + 64 * k];
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t t = uint32_t(__shfl_up(int(v), off));
-      if (lane >= off) v += t;
-    }
-    v += carry;
-    carry = uint32_t(__builtin_amdgcn_readlane(int(v), 63));
-    nx[k] += v;
-  }
-  __builtin_amdgcn_wave_barrier();
-}
-
-// The same placement with the rows' next free slots in registers (row lane + 64 k in
-// register k of that lane, read with readlane) for at most 64 * NREG rows: each round
-// walks the rows from the wavefront's lowest to its highest with one ballot per row.
-// Four wavefronts per block, each with its own chunk (blocks of one wavefront were held
-// back by the per-CU workgroup limit).
-template <int NREG>
-__global__ __launch_bounds__(256) void k_bin_rows_scatter_r(ViewTable vt, int64_t n, Records rec,
-                                                            const uint32_t* dvals, const unsigned long long* nvis,
-                                                            int64_t cap_vis, uint32_t* overflow, BinPlan plan) {
-  __shared__ unsigned long long s_part[256];
-  __shared__ uint32_t s_rr[4][kRowRuns + 1][64];  // per wavefront: the round's row runs
-  __shared__ uint32_t s_diff[4][64 * NREG + 1];     // per wavefront: rows covered (difference form)
-  if (blockIdx.x == gridDim.x - 1) rows_meta<256>(vt, plan, overflow, s_part);
-  const int R = plan.rows;
-  const int lane = threadIdx.x & 63, wv = int(threadIdx.x >> 6);
-  const int chunk = int(blockIdx.x) * 4 + int(threadIdx.x >> 6);  // one chunk per wavefront
-  const int64_t NV = clamp_count(nvis, cap_vis, overflow);
-  const int64_t beg = int64_t(chunk) * 64 * plan.rounds1;
-  if (chunk >= plan.nch1 || beg >= NV) return;
-  const uint32_t cap = uint32_t(min<int64_t>(plan.cap_M, int64_t(0xFFFFFFFFu)));
-  uint32_t nx[NREG];
-#pragma unroll
-  for (int k = 0; k < NREG; ++k) {
-    const int y = lane + 64 * k;
-    nx[k] = valu_copy(y < R ? plan.cnt1[int64_t(y) * plan.nch1 + chunk] : 0u);
-  }
-  for (int r = 0; r < plan.rounds1; ++r) {
-    const int64_t r0 = beg + int64_t(r) * 64;
-    if (r0 >= NV) break;
-    const int64_t i = r0 + lane;
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-    uint2 entry = make_uint2(0u, 0u);
-    if (i < NV) {
-      const uint32_t rid = dvals[i];
-      const uint2 rc = rec.rect[rid];
-      const int ro = vt.v[view_of_record(vt, rid, n)].row_off;
-      lo = uint32_t(ro) + (rc.y & 0xFFFFu);
-      hi = min(uint32_t(ro) + (rc.y >> 16), uint32_t(R - 1));
-      if (lo > hi) lo = 0xFFFFFFFFu;
-      entry = make_uint2(rid, rc.x);
-    }
-    const uint32_t first = lo;
-    // this lane's runs, row k of the splat at s_rr[wv][k][lane] (k = kRowRuns: the later
-    // rows); each lane reads back only its own column
-    if (rec.runs) {
-      uint32_t rr[kRowRuns];
-      load_row_runs(rec, entry, lo != 0xFFFFFFFFu, rr);
-#pragma unroll
-      for (int k = 0; k < kRowRuns; ++k) s_rr[wv][k][lane] = rr[k];
-      s_rr[wv][kRowRuns][lane] = entry.y | kRunUncut;
-    }
-    const uint32_t y0 = wave_min_u32(lo);
-    if (y0 == 0xFFFFFFFFu) continue;
-    const uint32_t y1 = wave_max_uniform_u32(lo != 0xFFFFFFFFu ? hi : 0u);
-    for (uint32_t y = y0; y <= y1; ++y) {  // branch-free but for the store
-      const bool on = lo <= y && y <= hi;
-      // (two ballots of plain compares: the compiler keeps them in scalar registers)
-      const uint64_t m = __builtin_amdgcn_ballot_w64(lo <= y) & __builtin_amdgcn_ballot_w64(y <= hi);
-      const uint32_t base = slot_of(nx, y);
-      const uint32_t dst = rank_below(m, base);
-      if (on && dst < cap) {
-        const uint32_t run = rec.runs ? s_rr[wv][min(y - first, uint32_t(kRowRuns))][lane] : entry.y;
-        plan.rowlist[dst] = make_uint2(entry.x, run);
+        for (int k = 0; k < kRowRuns; ++k) s_rr[k][t] = rr[k];
       }
+      s_rr[kRowRuns][t] = rec.runs ? entry.y | kRunUncut : entry.y;
+      s_rid[t] = entry.x;
+      s_first[t] = first;
+      place_round(L, nb, lo, hi, [&](uint32_t dst, int j, int bin) {
+        const uint32_t k = rec.runs ? min(uint32_t(w0 + bin) - s_first[j], uint32_t(kRowRuns)) : uint32_t(kRowRuns);
+        if (int64_t(dst) < plan.cap_M) plan.rowlist[dst] = make_uint2(s_rid[j], s_rr[k][j]);
+      });
     }
-    advance_slots(nx, s_diff[wv], lo, hi, lane);
   }
 }
 
@@ -1300,7 +1313,7 @@ struct Segment {
 __device__ __forceinline__ Segment segment_of(const ViewTable& vt, const BinPlan& plan, uint32_t s) {
   const int r = row_of_segment(plan.seg_start, plan.rows, s);
   const uint4 info = plan.rowinfo[r];
-  const uint32_t S2 = 64u * uint32_t(plan.rounds2);
+  const uint32_t S2 = uint32_t(kPlaceThreads) * uint32_t(plan.rounds2);
   Segment g;
   const uint32_t sidx = s - info.z;
   g.nseg = (info.y + S2 - 1) / S2;
@@ -1321,8 +1334,6 @@ __device__ __forceinline__ Segment segment_of(const ViewTable& vt, const BinPlan
 // not predict (a pixel stops once its transmittance is spent); when a previous forward
 // of the same tiles left those counts (`hint`), they are the key, else the list length.
 // ------------------------------------------------------------------------------------
-constexpr int kOrderBuckets = 257;
-
 __device__ __forceinline__ uint32_t work_bucket(uint32_t w) {
   if (w == 0) return 0;
   const uint32_t e = 31u - uint32_t(__clz(w));
@@ -1332,8 +1343,8 @@ __device__ __forceinline__ uint32_t work_bucket(uint32_t w) {
 
 // The queue order of `total` tiles by one whole block of NT threads (LDS: cnt and start
 // of kOrderBuckets words, red of NT / 64): bucket counts, their scan heaviest bucket first,
-// then each tile's slot (the order inside a bucket is arbitrary).  With a hint the ranges
-// are not read.
+// then each tile's slot (the order inside a bucket is arbitrary).  Key: the hint, or
+// without one the list length.
 template <int NT>
 __device__ void tile_order_block(const uint2* ranges, const uint32_t* hint, int total, uint32_t* order,
                                  uint32_t* cnt, uint32_t* start, uint32_t* red) {
@@ -1367,6 +1378,46 @@ __device__ void tile_order_block(const uint2* ranges, const uint32_t* hint, int 
   for (int i = t; i < total; i += NT) order[atomicAdd(&start[key(i)], 1u)] = uint32_t(i);
 }
 
+// The same order from a hint by many blocks, 256 tiles each, in the two kernels of the tile
+// stage: the count kernel's blocks add their tiles' buckets to global counters
+// (tile_order_count), the placement's blocks then know where every bucket starts and take
+// places in it (tile_order_place).  ord: kOrderBuckets counters and as many cursors, zero at the
+// start of the step.  (By one block, the order of 128k tiles took longer than the placement.)
+__device__ void tile_order_count(const uint32_t* hint, int total, uint32_t* ord, uint32_t* cnt) {
+  if (int(blockIdx.x) * 256 >= total) return;  // block-uniform
+  for (int b = threadIdx.x; b < kOrderBuckets; b += 256) cnt[b] = 0;
+  __syncthreads();
+  for (int i = int(blockIdx.x) * 256 + int(threadIdx.x); i < total; i += int(gridDim.x) * 256)
+    atomicAdd(&cnt[work_bucket(hint[i])], 1u);
+  __syncthreads();
+  for (int b = threadIdx.x; b < kOrderBuckets; b += 256)
+    if (cnt[b]) atomicAdd(&ord[b], cnt[b]);
+}
+
+__device__ void tile_order_place(const uint32_t* hint, int total, uint32_t* ord, uint32_t* order, uint32_t* cnt,
+                                 uint32_t* start, uint32_t* red) {
+  if (int(blockIdx.x) * 256 >= total) return;  // block-uniform
+  const int t = threadIdx.x;
+  for (int b = t; b < kOrderBuckets; b += 256) cnt[b] = 0;
+  __syncthreads();
+  // this block's tiles of each bucket (their rank in it is kept in the loop below, so count first)
+  for (int i = int(blockIdx.x) * 256 + t; i < total; i += int(gridDim.x) * 256) atomicAdd(&cnt[work_bucket(hint[i])], 1u);
+  // heaviest bucket first: position t of the descending order is bucket kOrderBuckets - 1 - t; bucket 0,
+  // the last, starts after all others
+  const uint32_t c = ord[kOrderBuckets - 1 - t];
+  const uint32_t ex = block_exclusive_scan_u32(c, red);  // (its barrier also completes cnt)
+  {
+    const int b = kOrderBuckets - 1 - t;
+    start[b] = ex + (cnt[b] ? atomicAdd(&ord[kOrderBuckets + b], cnt[b]) : 0u);
+    if (t == 255) start[0] = ex + c + (cnt[0] ? atomicAdd(&ord[kOrderBuckets], cnt[0]) : 0u);
+  }
+  static_assert(kOrderBuckets == 257, "one bucket per thread and bucket 0");
+  __syncthreads();
+  for (int i = int(blockIdx.x) * 256 + t; i < total; i += int(gridDim.x) * 256)
+    order[atomicAdd(&start[work_bucket(hint[i])], 1u)] = uint32_t(i);
+  __syncthreads();
+}
+
 __global__ __launch_bounds__(1024) void k_tile_order(const uint2* ranges, const uint32_t* hint, int total,
                                                     uint32_t* order) {
   __shared__ uint32_t cnt[kOrderBuckets], start[kOrderBuckets];
@@ -1374,28 +1425,29 @@ __global__ __launch_bounds__(1024) void k_tile_order(const uint2* ranges, const 
   tile_order_block<1024>(ranges, hint, total, order, cnt, start, red);
 }
 
-// stage 2 counts: tile-column histogram of one segment of a row list, one wavefront per
-// segment (its own LDS words, hist_stride >= tiles + 1: each run adds +1 at its first
-// column and -1 past its last, and a scan over the columns gives the counts).  With exact tiles the runs of a
+// stage 2 counts: tile-column histogram of one segment of a row list, one block per segment
+// (each run adds +1 at its first column and -1 past its last, and a scan over the columns
+// gives the counts).  With exact tiles the runs of a
 // record's first kRowRuns rows arrive cut by the projection; a run marked kRunUncut (a
 // later row of a tall splat) is cut here to the columns its ellipse reaches in this row
 // (row_run) and written back, so the placement below sees the same run; a row the
-// ellipse misses gets the empty run kRunEmpty (lo > hi).
+// ellipse misses gets the empty run kRunEmpty (lo > hi).  With a work hint the blocks also
+// count the tiles' order buckets.
 __global__ __launch_bounds__(256) void k_bin_tiles_count(ViewTable vt, BinPlan plan, Records rec, float exact_k,
-                                                         int tile, int hist_stride) {
-  extern __shared__ uint32_t hist_all[];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  uint32_t* hist = hist_all + wv * hist_stride;
+                                                         int tile, const uint32_t* hint) {
+  extern __shared__ uint32_t hist[];  // max_tiles_x + 1 words
+  __shared__ uint32_t s_cnt[kOrderBuckets], s_red[4], s_carry;
+  const int t = threadIdx.x;
+  if (hint) tile_order_count(hint, vt.total_tiles, plan.ord, s_cnt);
   const unsigned long long S = plan.words[1];
-  for (uint32_t s = blockIdx.x * 4u + uint32_t(wv); s < S; s += gridDim.x * 4u) {
+  for (uint32_t s = blockIdx.x; s < S; s += gridDim.x) {
     const Segment g = segment_of(vt, plan, s);
-    for (int i = lane; i <= g.tiles_x; i += 64) hist[i] = 0;
-    __builtin_amdgcn_wave_barrier();
-    // each entry is loaded one iteration ahead
-    uint2 e_next = g.beg + uint32_t(lane) < g.end ? plan.rowlist[g.beg + lane] : make_uint2(0u, kRunEmpty);
-    for (uint32_t i = g.beg + lane; i < g.end; i += 64) {
-      const uint2 e = e_next;
-      e_next = i + 64u < g.end ? plan.rowlist[i + 64u] : make_uint2(0u, kRunEmpty);
+    __syncthreads();
+    for (int i = t; i <= g.tiles_x; i += 256) hist[i] = 0;
+    if (t == 0) s_carry = 0;
+    __syncthreads();
+    for (uint32_t i = g.beg + uint32_t(t); i < g.end; i += 256) {
+      const uint2 e = plan.rowlist[i];
       uint32_t cx = e.y;
       if (cx & kRunUncut) {
         cx &= ~kRunUncut;
@@ -1415,19 +1467,17 @@ __global__ __launch_bounds__(256) void k_bin_tiles_count(ViewTable vt, BinPlan p
         atomicAdd(&hist[x1 + 1], 0xFFFFFFFFu);
       }
     }
-    __builtin_amdgcn_wave_barrier();
-    uint32_t carry = 0;  // inclusive scan over the columns, 64 at a time
-    for (int x = lane; x < ((g.tiles_x + 63) & ~63); x += 64) {
-      uint32_t v = x < g.tiles_x ? hist[x] : 0u;
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = uint32_t(__shfl_up(int(v), off));
-        if (lane >= off) v += t;
-      }
-      v += carry;
-      carry = uint32_t(__builtin_amdgcn_readlane(int(v), 63));
-      if (x < g.tiles_x) plan.cntF[g.flat + uint32_t(x) * g.nseg] = v;
+    __syncthreads();
+    for (int c0 = 0; c0 < g.tiles_x; c0 += 256) {  // inclusive scan over the columns, 256 at a time
+      const int x = c0 + t;
+      const uint32_t v = x < g.tiles_x ? hist[x] : 0u;
+      const uint32_t carry = s_carry;
+      const uint32_t in = block_exclusive_scan_u32(v, s_red) + v + carry;
+      if (x < g.tiles_x) plan.cntF[g.flat + uint32_t(x) * g.nseg] = in;
+      __syncthreads();
+      if (t == 255) s_carry = in;
+      __syncthreads();
     }
-    __builtin_amdgcn_wave_barrier();
   }
 }
 
@@ -1439,7 +1489,7 @@ __device__ __forceinline__ uint2 tile_range(const ViewTable& vt, const BinPlan& 
   const int local = t - cam.tile_off;
   const int r = cam.row_off + local / cam.tiles_x, x = local % cam.tiles_x;
   const uint4 info = plan.rowinfo[r];
-  const uint32_t S2 = 64u * uint32_t(plan.rounds2);
+  const uint32_t S2 = uint32_t(kPlaceThreads) * uint32_t(plan.rounds2);
   const uint32_t nseg = (info.y + S2 - 1) / S2;
   uint2 out = make_uint2(0u, 0u);
   if (nseg) {
@@ -1452,97 +1502,40 @@ __device__ __forceinline__ uint2 tile_range(const ViewTable& vt, const BinPlan& 
   return out;
 }
 
-// stage 2 placement: one wavefront per segment writes record ids into the tile lists; the
-// blocks first write the tile ranges (grid-stride over the tiles)
-__global__ __launch_bounds__(64) void k_bin_tiles_scatter(ViewTable vt, BinPlan plan, uint32_t* vals,
-                                                          const uint32_t* overflow, uint2* ranges) {
-  extern __shared__ uint32_t next[];  // next free slot of each tile for this segment
-  const int lane = threadIdx.x;
-  for (int t = int(blockIdx.x) * 64 + lane; t < vt.total_tiles; t += int(gridDim.x) * 64)
-    ranges[t] = tile_range(vt, plan, overflow, t);
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
+// stage 2 placement: one block per segment writes record ids into the tile lists; the blocks
+// first write the tile ranges (grid-stride over the tiles) and, with a work hint, the tile
+// queue's order
+__global__ __launch_bounds__(kPlaceThreads) void k_bin_tiles_place(ViewTable vt, BinPlan plan, uint32_t* vals,
+                                                                   const uint32_t* overflow, uint2* ranges,
+                                                                   const uint32_t* hint, uint32_t* order) {
+  extern __shared__ __align__(16) unsigned char s_dyn[];  // place_lds(bins) bytes, bins = min(max_tiles_x, kPlaceBins)
+  __shared__ uint32_t s_rid[kPlaceThreads];
+  const int t = threadIdx.x;
+  const PlaceLds L = place_carve(s_dyn, min(vt.max_tiles_x, kPlaceBins));
+  if (hint) {  // (in the stage's LDS, before the placement uses it)
+    uint32_t* cnt = reinterpret_cast<uint32_t*>(L.stage);
+    static_assert(kPlaceStage * 2 >= 2 * kOrderBuckets * 4, "the stage holds the counters and starts");
+    tile_order_place(hint, vt.total_tiles, plan.ord, order, cnt, cnt + kOrderBuckets, L.red);
+  }
+  for (int i = int(blockIdx.x) * kPlaceThreads + t; i < vt.total_tiles; i += int(gridDim.x) * kPlaceThreads)
+    ranges[i] = tile_range(vt, plan, overflow, i);
   const unsigned long long S = plan.words[1];
   for (uint32_t s = blockIdx.x; s < S; s += gridDim.x) {
     const Segment g = segment_of(vt, plan, s);
-    __syncthreads();
-    for (int i = lane; i < g.tiles_x; i += 64) next[i] = plan.cntF[g.flat + uint32_t(i) * g.nseg];
-    __syncthreads();
-    for (uint32_t r0 = g.beg; r0 < g.end; r0 += 64) {
-      const uint32_t i = r0 + uint32_t(lane);
-      uint32_t cur = 0xFFFFFFFFu, hi = 0u, rid = 0u;
-      if (i < g.end) {
-        const uint2 e = plan.rowlist[i];
-        rid = e.x;
-        cur = e.y & 0xFFFFu;
-        hi = min(e.y >> 16, uint32_t(g.tiles_x - 1));
-        if (cur > hi) cur = 0xFFFFFFFFu;  // a row the ellipse does not reach
+    for (int w0 = 0; w0 < g.tiles_x; w0 += kPlaceBins) {
+      const int nb = min(kPlaceBins, g.tiles_x - w0);
+      if (t < nb) L.next[t] = plan.cntF[g.flat + uint32_t(w0 + t) * g.nseg];
+      for (uint32_t r0 = g.beg; r0 < g.end; r0 += kPlaceThreads) {
+        const uint32_t i = r0 + uint32_t(t);
+        const uint2 e = i < g.end ? plan.rowlist[i] : make_uint2(0u, kRunEmpty);
+        const int lo = max(int(e.y & 0xFFFFu), w0) - w0;
+        const int hi = min(int(e.y >> 16), w0 + nb - 1) - w0;  // (lo > hi: a row the ellipse does not reach)
+        s_rid[t] = e.x;
+        __syncthreads();
+        place_round(L, nb, lo, hi, [&](uint32_t dst, int j, int) {
+          if (int64_t(dst) < plan.cap_M) vals[dst] = s_rid[j];
+        });
       }
-      for (uint32_t x = wave_min_u32(cur); x != 0xFFFFFFFFu; x = wave_min_u32(cur)) {
-        const bool on = cur == x;
-        const uint64_t m = __ballot(on);
-        const uint32_t base = next[x];
-        if (on) {
-          const uint32_t dst = base + uint32_t(__popcll(m & lt_mask));
-          if (int64_t(dst) < plan.cap_M) vals[dst] = rid;
-          cur = cur < hi ? cur + 1u : 0xFFFFFFFFu;
-        }
-        if (lane == 0) next[x] = base + uint32_t(__popcll(m));
-      }
-    }
-  }
-}
-
-// The same placement with the tiles' next free slots in registers (column lane + 64 k
-// in register k of that lane) for rows of at most 64 * NREG tiles; four wavefronts per
-// block, each with its own segments.
-template <int NREG>
-__global__ __launch_bounds__(256) void k_bin_tiles_scatter_r(ViewTable vt, BinPlan plan, uint32_t* vals,
-                                                             const uint32_t* overflow, uint2* ranges,
-                                                             const uint32_t* hint, uint32_t* order) {
-  __shared__ uint32_t s_cnt[kOrderBuckets], s_start[kOrderBuckets], s_red[4];
-  __shared__ uint32_t s_diff[4][64 * NREG + 1];  // per wavefront: tiles covered (difference form)
-  // with a work hint the tile queue's order does not need the ranges: the last block
-  // orders it here (no launch of its own)
-  if (hint && blockIdx.x == gridDim.x - 1) tile_order_block<256>(nullptr, hint, vt.total_tiles, order, s_cnt, s_start, s_red);
-  const int lane = threadIdx.x & 63;
-  for (int t = int(blockIdx.x) * 256 + int(threadIdx.x); t < vt.total_tiles; t += int(gridDim.x) * 256)
-    ranges[t] = tile_range(vt, plan, overflow, t);
-  const uint32_t cap = uint32_t(min<int64_t>(plan.cap_M, int64_t(0xFFFFFFFFu)));
-  const unsigned long long S = plan.words[1];
-  // a segment per wavefront
-  for (uint32_t s = blockIdx.x * 4u + (threadIdx.x >> 6); s < S; s += gridDim.x * 4u) {
-    const Segment g = segment_of(vt, plan, s);
-    uint32_t nx[NREG];
-#pragma unroll
-    for (int k = 0; k < NREG; ++k) {
-      const int x = lane + 64 * k;
-      nx[k] = valu_copy(x < g.tiles_x ? plan.cntF[g.flat + uint32_t(x) * g.nseg] : 0u);
-    }
-    // each round's entry is loaded one round ahead (its latency under the walk before it)
-    uint2 e_next = g.beg + uint32_t(lane) < g.end ? plan.rowlist[g.beg + lane] : make_uint2(0u, kRunEmpty);
-    for (uint32_t r0 = g.beg; r0 < g.end; r0 += 64) {
-      const uint32_t i = r0 + uint32_t(lane);
-      const uint2 e = e_next;
-      e_next = i + 64u < g.end ? plan.rowlist[i + 64u] : make_uint2(0u, kRunEmpty);
-      uint32_t lo = 0xFFFFFFFFu, hi = 0u, rid = 0u;
-      if (i < g.end) {
-        rid = e.x;
-        lo = e.y & 0xFFFFu;
-        hi = min(e.y >> 16, uint32_t(g.tiles_x - 1));
-        if (lo > hi) lo = 0xFFFFFFFFu;  // a row the ellipse does not reach
-      }
-      const uint32_t x0 = wave_min_u32(lo);
-      if (x0 == 0xFFFFFFFFu) continue;
-      const uint32_t x1 = wave_max_uniform_u32(lo != 0xFFFFFFFFu ? hi : 0u);
-      for (uint32_t x = x0; x <= x1; ++x) {  // branch-free but for the store
-        const bool on = lo <= x && x <= hi;
-        // (two ballots of plain compares: the compiler keeps them in scalar registers)
-        const uint64_t m = __builtin_amdgcn_ballot_w64(lo <= x) & __builtin_amdgcn_ballot_w64(x <= hi);
-        const uint32_t base = slot_of(nx, x);
-        const uint32_t dst = rank_below(m, base);
-        if (on && dst < cap) vals[dst] = rid;
-      }
-      advance_slots(nx, s_diff[threadIdx.x >> 6], lo, hi, lane);
     }
   }
 }
@@ -2591,48 +2584,51 @@ hipError_t launch_scan_pairs(uint2* blocksums, int count, unsigned long long* to
 
 hipError_t launch_compact(int64_t n, int views, const Records& rec, const uint2* blocksums, int nblk,
                           unsigned long long* totals, int64_t cap_M, uint32_t* dkeys, uint32_t* dvals,
-                          int64_t cap, uint32_t* overflow, bool raw, hipStream_t s) {
+                          int64_t cap, uint32_t* overflow, bool raw, uint32_t* vstart, hipStream_t s) {
   if (nblk == 0) return hipSuccess;
   if (raw && int64_t(views) * nblk > kCompactRawMax) return hipErrorInvalidValue;
   k_compact<<<dim3(nblk, views), kProjThreads, 0, s>>>(n, rec, blocksums, nblk, totals, cap_M, dkeys, dvals, cap,
-                                                        overflow, raw ? 1 : 0);
+                                                        overflow, raw ? 1 : 0, vstart);
   return hipGetLastError();
 }
 
 template <int BITS>
 static void radix_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, uint32_t* hist,
-                       uint32_t* digit_tot, const unsigned long long* count, int64_t cap, const uint32_t* overflow,
+                       uint32_t* digit_tot, const uint32_t* vstart, int views, const unsigned long long* count, int64_t cap, const uint32_t* overflow,
                        int shift, int nblk, hipStream_t s, Timer* tm) {
   if (tm) tm->begin(K_RADIX_HIST);
-  k_radix_hist<BITS><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, count, cap, overflow, shift, hist, nblk);
+  k_radix_hist<BITS><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, vstart, views, count, cap, overflow, shift, hist,
+                                                                 nblk);
   if (tm) tm->end(K_RADIX_HIST);
   if (tm) tm->begin(K_RADIX_ROWSCAN);
   k_radix_rowscan<<<1 << BITS, kSortThreads, 0, s>>>(hist, nblk, digit_tot);
   if (tm) tm->end(K_RADIX_ROWSCAN);
   if (tm) tm->begin(K_RADIX_SCATTER);
-  k_radix_scatter<BITS><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, vin, kout, vout, count, cap, overflow, shift, hist,
-                                                      digit_tot, nblk);
+  k_radix_scatter<BITS><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, vin, kout, vout, vstart, views, count, cap, overflow,
+                                                                    shift, hist, digit_tot, nblk);
   if (tm) tm->end(K_RADIX_SCATTER);
 }
 
-int radix_hist_words(int64_t cap) { return int((cap + kSortTile - 1) / kSortTile) << kSortBits; }
+// key tiles of at most cap keys: whole ones, and a partial one per view
+static int64_t sort_tiles(int64_t cap, int views) { return cap / kSortTile + views; }
+int64_t radix_hist_words(int64_t cap, int views) { return sort_tiles(cap, views) << kSortBits; }
 
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                             uint32_t* hist, uint32_t* digit_tot, const unsigned long long* count, int64_t cap,
-                             const uint32_t* overflow, int key_bits, bool* result_in_alt, int* passes, hipStream_t s,
-                             Timer* tm) {
+                             uint32_t* hist, uint32_t* digit_tot, const uint32_t* vstart, int views,
+                             const unsigned long long* count, int64_t cap, const uint32_t* overflow, int key_bits,
+                             bool* result_in_alt, int* passes, hipStream_t s, Timer* tm) {
   const int np = (key_bits + kSortBits - 1) / kSortBits;
   *passes = 0;
   *result_in_alt = false;
   if (cap <= 1 || np == 0) return hipSuccess;
   *passes = np;
-  const int nblk = int((cap + kSortTile - 1) / kSortTile);
+  const int nblk = int(sort_tiles(cap, views));
   uint32_t* kin = keys;
   uint32_t* vin = vals;
   uint32_t* kout = keys_alt;
   uint32_t* vout = vals_alt;
   for (int p = 0; p < np; ++p) {
-    radix_pass<kSortBits>(kin, vin, kout, vout, hist, digit_tot, count, cap, overflow, kSortBits * p, nblk, s, tm);
+    radix_pass<kSortBits>(kin, vin, kout, vout, hist, digit_tot, vstart, views, count, cap, overflow, kSortBits * p, nblk, s, tm);
     std::swap(kin, kout);
     std::swap(vin, vout);
   }
@@ -2641,17 +2637,17 @@ hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
 }
 
 BinPlan bin_plan(const ViewTable& vt, int64_t cap_vis, int64_t cap_M) {
-  // one 64-item round per wavefront (chunks and segments of 64: the most placement waves
-  // in parallel) while the count arrays stay within kMaxBinCounts entries; more rounds
-  // (fewer, longer chunks) beyond that
+  // one round of 256 items per block while the count arrays stay within kMaxBinCounts
+  // entries; more rounds (fewer, longer chunks and segments) beyond that
+  constexpr int64_t PT = kPlaceThreads;
   BinPlan p{};
   p.rows = vt.total_rows;
   const int64_t max_chunks = std::max<int64_t>(1, kMaxBinCounts / std::max(1, p.rows));
-  p.rounds1 = int(std::max<int64_t>(1, (cap_vis + 64 * max_chunks - 1) / (64 * max_chunks)));
-  p.nch1 = int(std::max<int64_t>(1, (cap_vis + 64 * p.rounds1 - 1) / (64 * p.rounds1)));
-  const int64_t max_segs = std::max<int64_t>(1024, kMaxBinCounts / std::max(1, vt.max_tiles_x));
-  p.rounds2 = int(std::max<int64_t>(1, (cap_M + 64 * max_segs - 1) / (64 * max_segs)));
-  const int64_t S2 = 64 * int64_t(p.rounds2);
+  p.rounds1 = int(std::max<int64_t>(1, (cap_vis + PT * max_chunks - 1) / (PT * max_chunks)));
+  p.nch1 = int(std::max<int64_t>(1, (cap_vis + PT * p.rounds1 - 1) / (PT * p.rounds1)));
+  const int64_t max_segs = std::max<int64_t>(1024, kMaxTileCounts / std::max(1, vt.max_tiles_x));
+  p.rounds2 = int(std::max<int64_t>(1, (cap_M + PT * max_segs - 1) / (PT * max_segs)));
+  const int64_t S2 = PT * int64_t(p.rounds2);
   const int64_t segs = (cap_M + S2 - 1) / S2;
   p.cap_M = cap_M;
   p.cap_seg = segs + p.rows;
@@ -2681,11 +2677,9 @@ hipError_t launch_bin(const ViewTable& vt, int64_t n, const Records& rec, const 
   auto B = [&](int k) { if (tm) tm->begin(k); };
   auto E = [&](int k) { if (tm) tm->end(k); };
   uint32_t* overflow = ctrl + kOverflow;
-  const size_t lds_rows = size_t(plan.rows) * 4, lds_cols = size_t(vt.max_tiles_x) * 4;
+  const size_t lds_rows = size_t(plan.rows) * 4;
   const int64_t n1 = int64_t(plan.rows) * plan.nch1;
-  const int g_count = int(std::min<int64_t>((plan.cap_seg + 3) / 4, 4096));
-  const int g_scatter = int(std::min<int64_t>(plan.cap_seg, 16384));
-  const int g_scatter4 = int(std::min<int64_t>((plan.cap_seg + 3) / 4, 4096));
+  const int g_segs = int(std::min<int64_t>(plan.cap_seg, 8192));
   B(K_BIN_COUNT);
   k_bin_rows_count<<<xcd_grid(plan.nch1), 256, lds_rows, s>>>(vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
   E(K_BIN_COUNT);
@@ -2693,32 +2687,18 @@ hipError_t launch_bin(const ViewTable& vt, int64_t n, const Records& rec, const 
   scan_u32(plan.cnt1, n1, nullptr, plan.part, plan.words, s);
   E(K_BIN_SCAN);
   B(K_BIN_SCATTER);
-  if (plan.rows <= 64)
-    k_bin_rows_scatter_r<1><<<(plan.nch1 + 3) / 4, 256, 0, s>>>(vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
-  else if (plan.rows <= 128)
-    k_bin_rows_scatter_r<2><<<(plan.nch1 + 3) / 4, 256, 0, s>>>(vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
-  else if (plan.rows <= 256)
-    k_bin_rows_scatter_r<4><<<(plan.nch1 + 3) / 4, 256, 0, s>>>(vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
-  else
-    k_bin_rows_scatter<<<plan.nch1, 64, lds_rows, s>>>(vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
+  k_bin_rows_place<<<xcd_grid(plan.nch1), kPlaceThreads, place_lds(std::min(plan.rows, kPlaceBins)), s>>>(vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
   E(K_BIN_SCATTER);
   B(K_BIN_COUNT);
-  k_bin_tiles_count<<<g_count, 256, 4 * (lds_cols + 4), s>>>(vt, plan, rec, exact_k, tile, vt.max_tiles_x + 1);
+  k_bin_tiles_count<<<g_segs, 256, (size_t(vt.max_tiles_x) + 1) * 4, s>>>(vt, plan, rec, exact_k, tile, hint);
   E(K_BIN_COUNT);
   B(K_BIN_SCAN);
   scan_u32(plan.cntF, plan.cap_flat, plan.words + 2, plan.part, plan.words + 3, s);
   E(K_BIN_SCAN);
   B(K_BIN_SCATTER);
-  if (vt.max_tiles_x <= 64)
-    k_bin_tiles_scatter_r<1><<<g_scatter4, 256, 0, s>>>(vt, plan, vals, overflow, ranges, hint, order);
-  else if (vt.max_tiles_x <= 128)
-    k_bin_tiles_scatter_r<2><<<g_scatter4, 256, 0, s>>>(vt, plan, vals, overflow, ranges, hint, order);
-  else if (vt.max_tiles_x <= 256)
-    k_bin_tiles_scatter_r<4><<<g_scatter4, 256, 0, s>>>(vt, plan, vals, overflow, ranges, hint, order);
-  else
-    k_bin_tiles_scatter<<<g_scatter, 64, lds_cols, s>>>(vt, plan, vals, overflow, ranges);
+  k_bin_tiles_place<<<g_segs, kPlaceThreads, place_lds(std::min(vt.max_tiles_x, kPlaceBins)), s>>>(vt, plan, vals, overflow, ranges, hint, order);
   E(K_BIN_SCATTER);
-  if (!hint || vt.max_tiles_x > 256) {  // the order not taken by the placement above
+  if (!hint) {  // the order not taken by the placement above
     B(K_TILE_ORDER);
     k_tile_order<<<1, 1024, 0, s>>>(ranges, hint, vt.total_tiles, order);
     E(K_TILE_ORDER);

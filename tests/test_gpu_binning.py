@@ -1,0 +1,44 @@
+"""GPU binning against the oracle's sorted keys: more tile columns and rows than one window of
+bins, more pairs in a round than one listing holds, chunks that span several small views."""
+import numpy as np
+import pytest
+
+import scenes
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from parity_util import check_keys, oracle_for, settings  # noqa: E402
+from test_gpu_parity import R, run_fwd, say  # noqa: E402, F401
+
+
+def _keys(R, g, cams, s):
+    _, _, saved = run_fwd(R, g, cams, s)
+    check_keys(saved.debug_export(), oracle_for(g, cams, s))
+    return saved.info()
+
+
+@pytest.mark.parametrize("exact", [False, True])
+@pytest.mark.parametrize("w,h,scale", [(2100, 40, 1.0), (40, 2100, 1.0), (2049, 2057, 1.0), (2048, 512, 12.0)])
+def test_many_columns_and_rows(R, w, h, scale, exact):
+    # tiles of 8: 263 and 257 bins are past one window of 256, 256 fill it; splats 12 times wider
+    # give rounds of 256 items more than 4,096 pairs
+    base = scenes.make_cfg1().gaussians
+    g = base.subset(np.arange(0, base.n, 2))
+    g.scales = (g.scales * scale).astype(np.float32)
+    f = float(max(w, h))
+    cam = scenes.Camera(w, h, f, f, w / 2.0, h / 2.0, np.eye(3, dtype=np.float32), np.zeros(3, np.float32))
+    say("bins", w, h, scale, exact)
+    info = _keys(R, g, [cam], settings(tile=8, exact_tiles=exact))
+    assert info["num_keys"] > (100 * g.n if scale > 1 else g.n)
+
+
+@pytest.mark.parametrize("n", [1, 5, 255, 257, 2000])
+def test_chunks_spanning_views(R, n):
+    # sixteen views of uneven sizes: a chunk of 256 depth-sorted records holds records of several
+    # views (n small), or the last of one and the first of the next
+    g = scenes.make_cfg1().gaussians.subset(np.arange(n))
+    c = scenes.make_cfg1().cameras[0]
+    cams = [c.crop(3 * k, 2 * k, 128 - 5 * k, 96 - 3 * k) for k in range(16)]
+    say("views", n)
+    _keys(R, g, cams, settings(tile=8, exact_tiles=n % 2 == 1))
