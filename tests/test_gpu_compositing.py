@@ -7,7 +7,7 @@ import scenes
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-from parity_util import settings  # noqa: E402
+from parity_util import settings, to_dev  # noqa: E402
 from test_gpu_parity import R, fwd_bwd_parity, say  # noqa: E402, F401
 
 
@@ -24,3 +24,33 @@ def test_clamped_splats_among_plain_ones(R, tile, every):
     say("clamped", tile, every)
     rep, grep = fwd_bwd_parity(R, g, [c, c.crop(13, 7, 37, 29)], settings(tile=tile, bg=(0.2, 0.1, 0.4)))
     say(rep, grep)
+
+
+@pytest.mark.parametrize("w,h", [(8, 8), (2048, 16), (512, 512), (520, 512), (1024, 600)])
+def test_backward_work_items_over_many_tiles(R, w, h):
+    # 1, 512, 4,096, 4,160 and 9,600 tiles of 8: the items of up to 4,096 are listed in queue order, of
+    # more by reservation; eager (twice over one saved state) and captured (replayed) backwards
+    # must agree up to the order of the float atomics
+    g = scenes.make_cfg1().gaussians
+    f = float(max(w, h))
+    cam = scenes.Camera(w, h, f, f, w / 2.0, h / 2.0, np.eye(3, dtype=np.float32), np.zeros(3, np.float32))
+    rng = np.random.default_rng(w + h)
+    target = (torch.from_numpy(rng.random((3, h, w), dtype=np.float32)).cuda(), None)
+    s = settings(tile=8)
+    params = to_dev(g)
+    say("items", w, h)
+    images, saved = R.forward(*params, [cam], s)
+    loss, gc, gd = R.loss_l1(saved, images, [target], 0.1)
+    first = R.backward(saved, gc)
+    second = R.backward(saved, gc)
+    graph = R.Graph(*params, [cam], [target], s)
+    replays = []
+    for _ in range(3):
+        graph.launch()
+        torch.cuda.synchronize()
+        replays.append({k: v.clone() for k, v in graph.grads.items()})
+    for other in [second] + replays:
+        for k in first:
+            scale = float(first[k].abs().max())
+            # float sums of the same terms in another order: 1e-5 of the group's largest value
+            assert float((first[k] - other[k]).abs().max()) <= 1e-5 * scale + 1e-20, (k, scale)
