@@ -280,6 +280,7 @@ gsr_status make_saved(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_camera* ca
       (st = alloc_in(sv, B, &sv->order, size_t(tiles))) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->loss_part, size_t(loss_partials(vt)))) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->ck.tile_nmax, size_t(tiles))) != GSR_OK ||
+      (st = alloc_in(sv, B, &sv->ck.slice_items, size_t(tiles / 256 + 1))) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->ck.acc, size_t(pix))) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->ck.state, size_t(tiles) * sv->ck.kmax * 5 * s->tile * s->tile)) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->ck.items, size_t(sv->ck.cap_items))) != GSR_OK ||

@@ -203,6 +203,7 @@ struct Ckpt {
   float* state;         // [tiles][kmax][5][pixels of a tile]: T, colour (3), depth in front
   float4* acc;          // [pixels] colour (3) and depth accumulated, without background
   uint32_t* tile_nmax;  // [tiles] longest contributor list of the tile
+  uint32_t* slice_items;  // [tiles / 256, rounded up] items of each 256 tiles of the queue
   uint2* items;         // [cap_items] backward work items (tile, first batch)
   int32_t kmax;         // checkpoints per tile
   int64_t cap_items;

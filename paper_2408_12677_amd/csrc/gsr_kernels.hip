@@ -1770,11 +1770,12 @@ __global__ __launch_bounds__(256) void k_count_used(ViewTable vt, Rules ru, Reco
 // tile's last checkpoint; one more item (tile, kmax) covers all later entries.  A block of 256
 // threads lists the 256 tiles of the queue from place 256 * slice: blocks of k_bwd_items, or in a
 // captured step the first blocks of the loss kernel.  Up to kListExact tiles every block adds up
-// the items in front of its slice itself, and the items are in queue order; beyond, it reserves
-// its items' places with one atomic (ctrl[kItems] zero before), in the order in which blocks
-// get there, about the queue's.  One block for all 128k tiles of sixteen 1752x1168 views made the
-// captured loss take 1252 us, now 304 (eight views of 876x584: 147 -> 51, one of 640x480: 12 ->
-// 9.6); one reservation per tile by the forward slowed that by a fifth over eight views.
+// the items in front of its slice itself; beyond, k_items_sum has added up each slice (a
+// block that reserved its places with an atomic instead got them in random order, and without
+// the longest-first order the backward over eight 876x584 views took 955 to 1213 us, with it 921).
+// One block for all 128k tiles of sixteen 1752x1168 views made the captured loss take 1252 us,
+// now 308 and 5 for the sums (eight views of 876x584: 147 -> 54 and 5, one of 640x480: 12 -> 9.6); one reservation per
+// tile by the forward slowed that by a fifth over eight views.
 constexpr int kListExact = 4096;
 
 __device__ __forceinline__ uint32_t tile_items(const uint32_t* order, int i, int stride, const Ckpt& ck, uint32_t& t) {
@@ -1783,31 +1784,31 @@ __device__ __forceinline__ uint32_t tile_items(const uint32_t* order, int i, int
   return nb <= uint32_t(ck.kmax) ? nb : uint32_t(ck.kmax) + 1u;
 }
 
+__global__ __launch_bounds__(256) void k_items_sum(const uint32_t* order, int total, int stride, Ckpt ck) {
+  __shared__ uint32_t red[4];
+  const int i = int(blockIdx.x * 256u + threadIdx.x);
+  uint32_t tile;
+  const uint32_t sum = block_sum_u32(i < total ? tile_items(order, i, stride, ck, tile) : 0u, red);
+  if (threadIdx.x == 0) ck.slice_items[blockIdx.x] = sum;
+}
+
 __device__ void list_bwd_items(int slice, const uint32_t* order, int total, int stride, const Ckpt& ck, uint32_t* ctrl,
                                uint32_t* red) {
   const int t = threadIdx.x, i = 256 * slice + t;
-  __shared__ uint32_t s_base;
   uint32_t tile = 0, u;
   const uint32_t ni = i < total ? tile_items(order, i, stride, ck, tile) : 0u;
   uint32_t before = 0;
   if (total <= kListExact) {
     for (int k = t; k < 256 * slice; k += 256) before += tile_items(order, k, stride, ck, u);
-    before = block_sum_u32(before, red);
+  } else {
+    for (int k = t; k < slice; k += 256) before += ck.slice_items[k];
   }
-  const uint32_t ex = block_exclusive_scan_u32(ni, red);
-  if (t == 255) {
-    const uint32_t sum = ex + ni;
-    if (total > kListExact)
-      s_base = sum ? atomicAdd(&ctrl[kItems], sum) : 0u;
-    else if (i + 1 >= total)  // the last slice
-      ctrl[kItems] = uint32_t(min<int64_t>(int64_t(before) + sum, ck.cap_items));
-  }
-  if (total > kListExact) {
-    __syncthreads();
-    before = s_base;
-  }
+  before = block_sum_u32(before, red);
+  const uint32_t at = before + block_exclusive_scan_u32(ni, red);
+  if (t == 255 && i + 1 >= total)  // the last slice
+    ctrl[kItems] = uint32_t(min<int64_t>(int64_t(at) + ni, ck.cap_items));
   for (uint32_t k = 0; k < ni; ++k)
-    if (int64_t(before) + ex + k < ck.cap_items) ck.items[before + ex + k] = make_uint2(tile, k);
+    if (int64_t(at) + k < ck.cap_items) ck.items[at + k] = make_uint2(tile, k);
 }
 
 __global__ __launch_bounds__(256) void k_bwd_items(const uint32_t* order, int total, int stride, Ckpt ck,
@@ -2830,9 +2831,16 @@ int loss_partials(const ViewTable& vt) {
   return int(blocks_for(maxp, 256)) * vt.nviews;
 }
 
+// the sums of the queue's slices, where list_bwd_items reads them
+static void launch_items_sum(const ViewTable& vt, int stride, const uint32_t* order, const Ckpt& ck, hipStream_t s) {
+  if (vt.total_tiles > kListExact)
+    k_items_sum<<<blocks_for(vt.total_tiles, 256), 256, 0, s>>>(order, vt.total_tiles, stride, ck);
+}
+
 hipError_t launch_loss_l1(const ViewTable& vt, float depth_w, float* part, float* loss, hipStream_t s,
                           const uint32_t* order, int batch, const Ckpt* ck, uint32_t* ctrl) {
   const int np = loss_partials(vt);
+  if (order) launch_items_sum(vt, ckpt_stride(batch), order, *ck, s);
   k_loss_l1<<<dim3(np / vt.nviews, vt.nviews), 256, 0, s>>>(vt, depth_w, part, order, vt.total_tiles,
                                                             ckpt_stride(batch), ck ? *ck : Ckpt{}, ctrl);
   if (loss) k_loss_sum<<<1, 256, 0, s>>>(part, np, loss);
@@ -2857,7 +2865,7 @@ hipError_t launch_blend_bwd(int tile, int batch, const ViewTable& vt, const Rule
                             hipStream_t s, bool items_listed) {
   if (vt.total_tiles == 0) return hipSuccess;
   if (!items_listed) {
-    if (vt.total_tiles > kListExact) k_fill_u32<<<1, 256, 0, s>>>(q.ctrl + kItems, 0u, 1);
+    launch_items_sum(vt, ckpt_stride(batch), q.order, ck, s);
     k_bwd_items<<<blocks_for(vt.total_tiles, 256), 256, 0, s>>>(q.order, vt.total_tiles, ckpt_stride(batch), ck, q.ctrl);
   }
   switch (tile) {

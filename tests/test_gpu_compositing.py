@@ -28,8 +28,8 @@ def test_clamped_splats_among_plain_ones(R, tile, every):
 
 @pytest.mark.parametrize("w,h", [(8, 8), (2048, 16), (512, 512), (520, 512), (1024, 600)])
 def test_backward_work_items_over_many_tiles(R, w, h):
-    # 1, 512, 4,096, 4,160 and 9,600 tiles of 8: the items of up to 4,096 are listed in queue order, of
-    # more by reservation; eager (twice over one saved state) and captured (replayed) backwards
+    # 1, 512, 4,096, 4,160 and 9,600 tiles of 8: up to 4,096 a slice of the queue counts
+    # the items in front of it itself, of more the slices are added up first; eager (twice over one saved state) and captured (replayed) backwards
     # must agree up to the order of the float atomics
     g = scenes.make_cfg1().gaussians
     f = float(max(w, h))
