@@ -275,7 +275,7 @@ gsr_status make_saved(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_camera* ca
       (st = alloc_in(sv, B, &sv->rec.rgb, VN)) != GSR_OK || (st = alloc_in(sv, B, &sv->rec.rect, VN)) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->rec.counts, VN)) != GSR_OK ||
       ((s->flags & GSR_EXACT_TILES) && (st = alloc_in(sv, B, &sv->rec.runs, size_t(VN) * kRowRuns)) != GSR_OK) ||
-      (st = alloc_in(sv, B, &sv->blocksums, size_t(V) * sv->nblk + 1)) != GSR_OK ||
+      (st = alloc_in(sv, B, &sv->blocksums, size_t(scan_pairs_words(int64_t(V) * sv->nblk)) + 1)) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->d_total, 4)) != GSR_OK || (st = alloc_in(sv, B, &sv->ranges, size_t(tiles))) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->order, size_t(tiles))) != GSR_OK ||
       (st = alloc_in(sv, B, &sv->loss_part, size_t(loss_partials(vt)))) != GSR_OK ||
@@ -381,7 +381,7 @@ void keep_hint(gsr_ctx* ctx, const gsr_saved* sv, hipStream_t s) {
 }
 
 // Whether the compaction scans the projection's block sums itself (see launch_compact).
-bool compact_scans(const gsr_saved* sv) { return sv->graph && int64_t(sv->V) * sv->nblk <= kCompactRawMax; }
+bool raw_sums(const gsr_saved* sv) { return sv->graph && compact_scans(int64_t(sv->V) * sv->nblk); }
 
 // Phase A of a forward: clear the control words, project, scan the block sums.
 hipError_t enqueue_project(gsr_saved* sv, hipStream_t s, bool timing) {
@@ -398,8 +398,8 @@ hipError_t enqueue_project(gsr_saved* sv, hipStream_t s, bool timing) {
   });
   // a captured step with few block sums leaves their scan to the compaction (the host
   // does not read the totals); an eager forward reads them to size its buffers
-  if (e == hipSuccess && !compact_scans(sv))
-    e = T(K_SCAN, [&] { return launch_scan_pairs(sv->blocksums, sv->V * sv->nblk, sv->d_total, s); });
+  if (e == hipSuccess && !raw_sums(sv))
+    e = T(K_SCAN, [&] { return launch_scan_pairs(sv->blocksums, int64_t(sv->V) * sv->nblk, sv->d_total, s); });
   return e;
 }
 
@@ -418,7 +418,7 @@ hipError_t enqueue_sort_blend(gsr_saved* sv, hipStream_t s, bool timing) {
     bool alt = false;
     e = T(K_COMPACT, [&] {
       return launch_compact(sv->N, sv->V, sv->rec, sv->blocksums, sv->nblk, sv->d_total, sv->cap_M, sv->dk, sv->dv,
-                            sv->cap_vis, ovf, compact_scans(sv), sv->vstart, s);
+                            sv->cap_vis, ovf, raw_sums(sv), sv->vstart, s);
     });
     if (e == hipSuccess)
       // depth keys are the bits of a positive binary32 depth: bit 31 is zero

@@ -291,11 +291,14 @@ hipError_t launch_scan_small(uint32_t* a, int count, unsigned long long* total, 
 hipError_t launch_project(int deg, const GaussDev& g, const ViewTable& vt, const Rules& ru, int tile,
                           const Records& rec, uint2* blocksums, int nblk, float* zero_rows, uint32_t* ctrl,
                           int clear_words, float exact_k, hipStream_t s);
-hipError_t launch_scan_pairs(uint2* blocksums, int count, unsigned long long* totals, hipStream_t s);
-// raw: blocksums as the projection wrote them (not scanned; at most kCompactRawMax of
-// them), and the compaction writes totals[0..1] itself; else scanned by launch_scan_pairs,
+// Scans the projection's count block sums (an array of scan_pairs_words(count) pairs) for the
+// compaction and writes the totals.
+int64_t scan_pairs_words(int64_t count);
+hipError_t launch_scan_pairs(uint2* blocksums, int64_t count, unsigned long long* totals, hipStream_t s);
+// raw: blocksums as the projection wrote them (not scanned; allowed where compact_scans),
+// and the compaction writes totals[0..1] itself; else scanned by launch_scan_pairs,
 // which wrote the totals.  vstart gets views + 1 words: where each view's records start.
-constexpr int64_t kCompactRawMax = 4096;
+bool compact_scans(int64_t count);
 hipError_t launch_compact(int64_t n, int views, const Records& rec, const uint2* blocksums, int nblk,
                           unsigned long long* totals, int64_t cap_M, uint32_t* dkeys, uint32_t* dvals,
                           int64_t cap, uint32_t* overflow, bool raw, uint32_t* vstart, hipStream_t s);

@@ -3,7 +3,7 @@
 //   K1 k_project        per Gaussian, loop over views: Eq. 2, 4, 5 (+ low-pass), conic of
 //                       the 2D splat (Eq. 3), SH colour, frustum cull, tile rectangle, tile count,
 //                       block sums of the tile counts and of the visible records
-//   K2 k_scan_pairs     exclusive scans of those block sums (one block)
+//   K2 k_scan_pairs     exclusive scans of those block sums (one block, or of many by tiles)
 //   K3/K4               the stable sort of the (tile id << 32 | depth bits) keys, without
 //                       materialising them: k_compact + k_radix_* sort the visible records by
 //                       depth bits (stable LSD, 8-bit digits: histogram / row scan /
@@ -632,6 +632,49 @@ __global__ __launch_bounds__(1024) void k_scan_u32(uint32_t* a, int count, unsig
   if (t == 1023) *total = incl;
 }
 
+// The same scan of more than kSumMany pairs, in place, by tiles of kSumTile: their sums, then each
+// block adds up the sums in front of its tile and scans it.  One block over all 188k block sums
+// of sixteen views of 3M Gaussians took 336 us and over the 15k of eight views of 500k 32 us;
+// the two launches take 11 and 10.  With fewer the second launch costs what it saves.
+constexpr int kSumTile = 256;
+constexpr int64_t kSumMany = 4096;
+
+__global__ __launch_bounds__(kSumTile) void k_sum_pairs(const uint2* a, int64_t count, uint2* part) {
+  __shared__ uint32_t red[kSumTile / 64];
+  const int64_t i = int64_t(blockIdx.x) * kSumTile + threadIdx.x;
+  const uint2 v = i < count ? a[i] : make_uint2(0u, 0u);
+  const uint32_t x = block_sum_u32(v.x, red), y = block_sum_u32(v.y, red);
+  if (threadIdx.x == 0) part[blockIdx.x] = make_uint2(x, y);
+}
+
+__global__ __launch_bounds__(kSumTile) void k_scan_pairs_down(uint2* a, int64_t count, const uint2* part,
+                                                              unsigned long long* totals) {
+  __shared__ unsigned long long red[kSumTile];
+  const int t = threadIdx.x;
+  unsigned long long bx = 0, by = 0;
+  for (int i = t; i < int(blockIdx.x); i += kSumTile) {
+    const uint2 p = part[i];
+    bx += p.x;
+    by += p.y;
+  }
+  const int64_t i = int64_t(blockIdx.x) * kSumTile + t;
+  const uint2 v = i < count ? a[i] : make_uint2(0u, 0u);
+  (void)block_inclusive_scan_u64<kSumTile>(bx, red);
+  const unsigned long long x0 = red[kSumTile - 1];
+  __syncthreads();
+  (void)block_inclusive_scan_u64<kSumTile>(by, red);
+  const unsigned long long y0 = red[kSumTile - 1];
+  __syncthreads();
+  const unsigned long long ix = x0 + block_inclusive_scan_u64<kSumTile>(v.x, red);
+  __syncthreads();
+  const unsigned long long iy = y0 + block_inclusive_scan_u64<kSumTile>(v.y, red);
+  if (i < count) a[i] = make_uint2(uint32_t(ix - v.x), uint32_t(iy - v.y));
+  if (i == count - 1) {
+    totals[0] = ix;
+    totals[1] = iy;
+  }
+}
+
 // Flags a capacity overflow: the step's word and the sticky copy next to it.
 __device__ __forceinline__ void raise_overflow(uint32_t* overflow) {
   atomicOr(overflow, 1u);
@@ -651,10 +694,10 @@ __device__ __forceinline__ uint32_t clamp_count(const unsigned long long* count,
 // ------------------------------------------------------------------------------------
 // K3a: compaction of the visible records into (depth bits, record id) pairs, record order
 // ------------------------------------------------------------------------------------
-// raw: the block sums are the projection's, not scanned (at most kCompactRawMax of them):
+// raw: the block sums are the projection's, not scanned (at most kSumMany of them):
 // each block adds the visible records of the blocks in front of it itself, and the last
 // block writes the totals (pairs, visible records) to totals[0..1].  Otherwise they were
-// scanned (k_scan_pairs, which wrote the totals).  vstart[0 .. views]: where each view's
+// scanned (launch_scan_pairs, which wrote the totals).  vstart[0 .. views]: where each view's
 // records start, and their end.
 __global__ __launch_bounds__(kProjThreads) void k_compact(int64_t n, Records rec, const uint2* blocksums, int nblk,
                                                           unsigned long long* totals, int64_t cap_M,
@@ -2598,16 +2641,26 @@ hipError_t launch_scan_small(uint32_t* a, int count, unsigned long long* total, 
   return hipGetLastError();
 }
 
-hipError_t launch_scan_pairs(uint2* blocksums, int count, unsigned long long* totals, hipStream_t s) {
-  k_scan_pairs<<<1, 1024, 0, s>>>(blocksums, count, totals);
+int64_t scan_pairs_words(int64_t count) { return count + (count > kSumMany ? (count + kSumTile - 1) / kSumTile : 0); }
+
+hipError_t launch_scan_pairs(uint2* blocksums, int64_t count, unsigned long long* totals, hipStream_t s) {
+  if (count > kSumMany) {
+    const int tiles = blocks_for(count, kSumTile);
+    k_sum_pairs<<<tiles, kSumTile, 0, s>>>(blocksums, count, blocksums + count);
+    k_scan_pairs_down<<<tiles, kSumTile, 0, s>>>(blocksums, count, blocksums + count, totals);
+  } else {
+    k_scan_pairs<<<1, 1024, 0, s>>>(blocksums, int(count), totals);
+  }
   return hipGetLastError();
 }
+
+bool compact_scans(int64_t count) { return count <= kSumMany; }
 
 hipError_t launch_compact(int64_t n, int views, const Records& rec, const uint2* blocksums, int nblk,
                           unsigned long long* totals, int64_t cap_M, uint32_t* dkeys, uint32_t* dvals,
                           int64_t cap, uint32_t* overflow, bool raw, uint32_t* vstart, hipStream_t s) {
   if (nblk == 0) return hipSuccess;
-  if (raw && int64_t(views) * nblk > kCompactRawMax) return hipErrorInvalidValue;
+  if (raw && !compact_scans(int64_t(views) * nblk)) return hipErrorInvalidValue;
   k_compact<<<dim3(nblk, views), kProjThreads, 0, s>>>(n, rec, blocksums, nblk, totals, cap_M, dkeys, dvals, cap,
                                                         overflow, raw ? 1 : 0, vstart);
   return hipGetLastError();

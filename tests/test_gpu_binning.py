@@ -8,7 +8,7 @@ import scenes
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-from parity_util import check_keys, oracle_for, settings  # noqa: E402
+from parity_util import check_keys, oracle_for, settings, to_dev  # noqa: E402
 from test_gpu_parity import R, run_fwd, say  # noqa: E402, F401
 
 
@@ -42,3 +42,29 @@ def test_chunks_spanning_views(R, n):
     cams = [c.crop(3 * k, 2 * k, 128 - 5 * k, 96 - 3 * k) for k in range(16)]
     say("views", n)
     _keys(R, g, cams, settings(tile=8, exact_tiles=n % 2 == 1))
+
+
+@pytest.mark.parametrize("views,n", [(1, 1), (3, 1365 * 256), (16, 65536), (16, 65537), (3, 1366 * 256), (16, 200000)])
+def test_block_sums_of_many_gaussians(R, views, n):
+    # block sums of 256 records each: 1, 4,095 and 4,096 are scanned by one block, 4,112, 4,098 and
+    # 12,512 by tiles of 256; captured steps leave up to 4,096 to the compaction.  Splats of a
+    # twentieth of the size: hundreds of thousands of records whose tile lists stay short
+    base = scenes.make_cfg1().gaussians
+    rng = np.random.default_rng(n)
+    g = base.subset(rng.integers(0, base.n, n))
+    g.means = (g.means + rng.normal(0, 0.05, g.means.shape)).astype(np.float32)
+    g.scales = (g.scales * 0.05).astype(np.float32)
+    c = scenes.make_cfg1().cameras[0]
+    cams = [c.crop(k, 2 * k, 64 - 2 * k, 48 - k) for k in range(views)]
+    say("block sums", views, n)
+    s = settings(tile=16)
+    _keys(R, g, cams, s)
+    params = to_dev(g)
+    images, _ = R.forward(*params, cams, s)
+    target = [(torch.zeros_like(im[0]), None) for im in images]
+    graph = R.Graph(*params, cams, target, s)
+    for _ in range(3):
+        graph.launch()
+        graph.sync()   # raises where a capacity overflowed
+        for a, b in zip(graph.images, images):
+            assert torch.equal(a[0], b[0])
