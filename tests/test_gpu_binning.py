@@ -68,3 +68,52 @@ def test_block_sums_of_many_gaussians(R, views, n):
         graph.sync()   # raises where a capacity overflowed
         for a, b in zip(graph.images, images):
             assert torch.equal(a[0], b[0])
+
+
+class _Pieces:
+    """A caller's allocator that refuses blocks above `limit` bytes."""
+
+    def __init__(self, limit):
+        self.limit, self.held, self.asked = limit, {}, []
+
+    def alloc(self, nbytes, stream):
+        self.asked.append(nbytes)
+        if nbytes > self.limit:
+            return 0
+        t = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+        p = (t.data_ptr() + 255) // 256 * 256
+        self.held[p] = t
+        return p
+
+    def free(self, ptr, stream):
+        torch.cuda.synchronize()
+        del self.held[ptr]
+
+
+@pytest.mark.parametrize("limit,separate", [(1 << 40, False), (1000000, True), (8 << 10, None)])
+def test_allocator_that_refuses_one_large_block(R, limit, separate):
+    # the arrays of a forward (the largest takes 983,040 bytes) come as one block, or where that
+    # is refused one by one; where an
+    # array is refused too the call fails and gives everything back
+    g = scenes.make_cfg1().gaussians.subset(np.arange(400))
+    cam = scenes.make_cfg1().cameras[0].crop(0, 0, 64, 48)
+    params, s = to_dev(g), settings(tile=16)
+    images, saved = R.forward(*params, [cam], s)
+    grads = R.backward(saved, [torch.ones_like(images[0][0])])
+    pieces = _Pieces(limit)
+    ctx = R.Context(torch.cuda.current_device(), torch.cuda.current_stream().cuda_stream, pieces)
+    say("allocator", limit)
+    with R.using(ctx):
+        if separate is None:
+            with pytest.raises(Exception, match="ENOMEM"):
+                R.forward(*params, [cam], s)
+            assert not pieces.held
+            return
+        images2, saved2 = R.forward(*params, [cam], s)
+        grads2 = R.backward(saved2, [torch.ones_like(images[0][0])])
+    assert (max(pieces.asked) > limit) == separate
+    for a, b in zip(images[0], images2[0]):
+        assert torch.equal(a, b)
+    for k in grads:
+        assert float((grads[k] - grads2[k]).abs().max()) <= 1e-5 * float(grads[k].abs().max()) + 1e-20
+    saved2.free()
