@@ -447,8 +447,8 @@ hipError_t enqueue_sort_blend(gsr_saved* sv, hipStream_t s, bool timing) {
     });
     if (e == hipSuccess)
       // depth keys are the bits of a positive binary32 depth: bit 31 is zero
-      e = launch_radix_sort(sv->dk, sv->dv, sv->dk2, sv->dv2, sv->hist, sv->dtot, sv->vstart, sv->V, sv->d_total + 1,
-                            sv->cap_vis, ovf, 31, &alt, &sv->sort_passes, s, tm);
+      e = launch_radix_sort(sv->dk, sv->dv, sv->dk2, sv->dv2, sv->hist, sv->dtot, sv->vstart, sv->V, sv->N,
+                            sv->d_total + 1, sv->cap_vis, ovf, 31, &alt, &sv->sort_passes, s, tm);
     if (alt) sorted = sv->dv2;
   }
   if (e == hipSuccess)

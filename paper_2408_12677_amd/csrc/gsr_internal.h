@@ -98,9 +98,6 @@ struct Timer {
 };
 
 constexpr int kProjThreads = 256;  // Gaussians per block in the per-Gaussian kernels
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 4;
-constexpr int kSortTile = kSortThreads * kSortItems;  // keys per radix-sort block
 constexpr int kGrad2D = 12;  // floats per (view, Gaussian) 2D-gradient record (10 used)
 constexpr int kHeadFwd = 0;    // control words (see TileQueue)
 constexpr int kHeadBwd = 1;
@@ -308,12 +305,12 @@ int ckpt_stride(int batch);
 int ckpt_per_tile(int batch);
 int64_t bwd_items_cap(int total_tiles, int batch);
 // Stable LSD radix sort of min(*count, cap) (key, value) pairs by their key_bits low bits
-// (at most 32; 8-bit passes), each view's keys (places vstart[v] .. vstart[v + 1], device) by
-// themselves; the result is in the _alt arrays when *result_in_alt.  hist holds
+// (at most 32; 8-bit passes), each view's keys (places vstart[v] .. vstart[v + 1], device; at most
+// per_view of them) by themselves; the result is in the _alt arrays when *result_in_alt.  hist holds
 // radix_hist_words(cap, views) words, digit_tot 256.
 int64_t radix_hist_words(int64_t cap, int views);
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                             uint32_t* hist, uint32_t* digit_tot, const uint32_t* vstart, int views,
+                             uint32_t* hist, uint32_t* digit_tot, const uint32_t* vstart, int views, int64_t per_view,
                              const unsigned long long* count, int64_t cap, const uint32_t* overflow, int key_bits,
                              bool* result_in_alt, int* passes, hipStream_t s, Timer* tm);
 // Sizes of a binning plan for capacities (cap_vis, cap_M); pointers are left null.

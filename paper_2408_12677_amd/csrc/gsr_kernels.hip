@@ -82,10 +82,25 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
   return v;
 }
 
+// Inclusive sum over the wavefront (DPP row shifts, then the rows' totals broadcast to the
+// rows behind).  Needs every lane active.
+__device__ __forceinline__ uint32_t wave_add_scan(uint32_t v) {
+#define GSR_ADD_STEP(CTRL, ROWS) \
+  v += uint32_t(__builtin_amdgcn_update_dpp(0, int(v), CTRL, ROWS, 0xF, false))
+  GSR_ADD_STEP(0x111, 0xF);  // row_shr:1
+  GSR_ADD_STEP(0x112, 0xF);
+  GSR_ADD_STEP(0x114, 0xF);
+  GSR_ADD_STEP(0x118, 0xF);
+  GSR_ADD_STEP(0x142, 0xA);  // row_bcast:15
+  GSR_ADD_STEP(0x143, 0xC);  // row_bcast:31
+#undef GSR_ADD_STEP
+  return v;
+}
+
 __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_add_scan(v);
   const int nw = blockDim.x >> 6;
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 63) red[threadIdx.x >> 6] = v;
   __syncthreads();
   uint32_t tot = 0;
   for (int i = 0; i < nw; ++i) tot += red[i];
@@ -95,11 +110,7 @@ __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
 
 __device__ __forceinline__ uint32_t block_exclusive_scan_u32(uint32_t v, uint32_t* red) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  uint32_t incl = v;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t t = __shfl_up(incl, off);
-    if (lane >= off) incl += t;
-  }
+  const uint32_t incl = wave_add_scan(v);
   if (lane == 63) red[w] = incl;
   __syncthreads();
   uint32_t pre = 0;
@@ -750,22 +761,39 @@ __global__ __launch_bounds__(kProjThreads) void k_compact(int64_t n, Records rec
 }
 
 // ------------------------------------------------------------------------------------
-// K4: stable LSD radix sort of (u32 key, u32 value) by digits of BITS bits, each view's
+// K4: stable LSD radix sort of (u32 key, u32 value) by 8-bit digits, each view's
 // keys by themselves (the compaction leaves them in view order, and a tile's list needs no
 // order between views; records in view order let the binning handle one view's tile rows at
-// a time).  A key tile is kSortTile keys of one view; counts are read from the device
+// a time).  A key tile is ITEMS keys a thread of one view; counts are read from the device
 // (clamped to the capacity the grid was sized for).  Per pass:
-//   hist:    per-tile digit histograms, stored digit-major [2^BITS][ntile]
-//   rowscan: one block per digit scans its row -> keys of the digit in front of each tile,
-//            and the digit total
-//   scatter: each block ranks its keys stably (wavefront multisplit by ballots, then
-//            across the four wavefronts through LDS) and writes them to their slots: the
-//            view's start, its keys of smaller digits and the row's count since the view's
-//            first tile
+//   hist:    per-tile digit histograms
+//   rowscan: (views of more than kSortFold tiles, histograms digit-major [256][ntile]) one block
+//            per digit scans its row -> keys of the digit in front of each tile, and the digit total.
+//            With fewer the histograms are tile-major [ntile][256] and each block of the
+//            scatter adds up its view's itself: a launch less
+//   scatter: each block ranks its keys stably, orders them in LDS, and writes them out in
+//            runs: a key's slot is the view's start, its keys of smaller digits, the digit's keys
+//            in the view's tiles in front and its rank in the tile
+// A wavefront owns 64 ITEMS consecutive keys, so that it ranks them by itself (peers of a
+// digit by ballots, a counter per digit of its own in LDS), and the block meets at a barrier
+// only to add up the wavefronts' counters (four rounds of 256 keys with two barriers each, and
+// a store per key, before).  Views of up to kSmallMost keys are sorted by one block each, in LDS,
+// all passes in one launch.
+// Kernel trace of a whole sort, before -> after: 1.9k keys 43 -> 13 us, 12k 49 -> 41, 85k 51 -> 39,
+// 335k 73 -> 51 (captured), 1M 103 -> 70, 2.7M in eight views 231 -> 126.  The small ones are chains of latencies (2 us of each launch), the large ones VALU
+// issue of the ranking (half) and the scattered writes.
 // ------------------------------------------------------------------------------------
 // 8-bit digits: wider ones (11 bits, three passes for a depth key) ran slower on MI355X,
-// their digit-major histograms being written and read across many more cache lines
-constexpr int kSortBits = 8;
+// their histograms being written and read across many more cache lines
+constexpr int kSortBits = 8, kSortDigits = 1 << kSortBits;
+constexpr int kSortThreads = 1024, kSortWaves = kSortThreads / 64;
+// Keys of a thread: 4 (tiles of 4,096), or 2 where that still folds: 85k keys sort in 39 us with
+// 2 and 49 with 4, 335k in 51 and 55, eight views of 340k in 170 and 126.
+constexpr int kSortItems = 4, kSortItemsFew = 2;
+// A view's tiles up to which the scatter adds up the histograms itself: at 102 tiles a captured sort
+// takes 55 us with it and 70 with the row scans, at 162 61 and 63, at 245 75 and 70.
+constexpr int kSortFold = 224;
+constexpr int64_t kSmallMost = 16 * kSortThreads;
 
 // Block b of a grid of G blocks (G a multiple of 8) as index (b mod 8) * (G / 8) + b / 8:
 // the hardware hands consecutive blocks to the eight XCDs in turn, so with this index
@@ -775,74 +803,151 @@ constexpr int kSortBits = 8;
 __device__ __forceinline__ int xcd_block(int b, int G) { return (b & 7) * (G >> 3) + (b >> 3); }
 static int xcd_grid(int64_t blocks) { return int((blocks + 7) / 8 * 8); }
 
-
 // The keys of tile tb: its view's first key and end (in the key arrays), this tile's first key, the view's
 // first tile and the next view's (ntile: past the last).  False past the last tile.
 struct SortTile {
   uint32_t vbeg, vend, beg;
   int t0, t1;
 };
+// (every lane active; lane v looks up view v, all loads in flight together)
+template <int ITEMS>
 __device__ __forceinline__ bool sort_tile(const uint32_t* vstart, int views, const unsigned long long* count, int64_t cap,
                                           const uint32_t* overflow, int tb, SortTile& o) {
-  const uint32_t M = clamp_count(count, cap, overflow);
-  o.t1 = 0;
-  for (int v = 0; v < views; ++v) {
-    o.vbeg = min(vstart[v], M);
-    o.vend = min(vstart[v + 1], M);
-    o.t0 = o.t1;
-    o.t1 += int((o.vend - o.vbeg + kSortTile - 1) / kSortTile);
-    if (tb < o.t1) {
-      o.beg = o.vbeg + uint32_t(tb - o.t0) * kSortTile;
-      return true;
-    }
-  }
-  return false;
+  static_assert(GSR_MAX_VIEWS <= 16, "a view per lane of a DPP row");
+  constexpr uint32_t kTile = ITEMS * kSortThreads;
+  const int lane = threadIdx.x & 63;
+  const uint32_t a = vstart[min(lane, views)], b = vstart[min(lane + 1, views)];
+  const unsigned long long c = *count;
+  const uint32_t over = *overflow;
+  const uint32_t M = over ? 0u : uint32_t(c < (unsigned long long)cap ? c : (unsigned long long)cap);
+  const uint32_t beg = min(a, M), end = min(b, M);  // (empty past the last view)
+  const uint32_t tiles = (end - beg + kTile - 1) / kTile;
+  uint32_t incl = tiles;
+#define GSR_ADD_STEP(CTRL) incl += uint32_t(__builtin_amdgcn_update_dpp(0, int(incl), CTRL, 0xF, 0xF, false))
+  GSR_ADD_STEP(0x111);  // row_shr:1
+  GSR_ADD_STEP(0x112);
+  GSR_ADD_STEP(0x114);
+  GSR_ADD_STEP(0x118);
+#undef GSR_ADD_STEP
+  const uint64_t past = __ballot(lane < views && uint32_t(tb) < incl);
+  if (past == 0) return false;
+  const int v = __builtin_ctzll(past);
+  o.vbeg = uint32_t(__builtin_amdgcn_readlane(int(beg), v));
+  o.vend = uint32_t(__builtin_amdgcn_readlane(int(end), v));
+  o.t1 = __builtin_amdgcn_readlane(int(incl), v);
+  o.t0 = o.t1 - __builtin_amdgcn_readlane(int(tiles), v);
+  o.beg = o.vbeg + uint32_t(tb - o.t0) * kTile;
+  return true;
 }
 
-template <int BITS>
+template <int ITEMS, bool FOLD>
 __global__ __launch_bounds__(kSortThreads) void k_radix_hist(const uint32_t* keys, const uint32_t* vstart, int views,
                                                              const unsigned long long* count, int64_t cap,
                                                              const uint32_t* overflow, int shift, uint32_t* hist,
                                                              int nblk) {
-  constexpr int D = 1 << BITS;
-  constexpr uint32_t MASK = D - 1;
-  __shared__ uint32_t h[D];
+  __shared__ uint32_t h[kSortDigits];
+  const int t = threadIdx.x;
   const int tb = xcd_block(blockIdx.x, gridDim.x);  // this block's tile of keys
   if (tb >= nblk) return;                            // block-uniform
-  for (int d = threadIdx.x; d < D; d += kSortThreads) h[d] = 0;
+  if (t < kSortDigits) h[t] = 0;
   __syncthreads();
   SortTile st;
-  if (sort_tile(vstart, views, count, cap, overflow, tb, st)) {
-#pragma unroll 4
-    for (int i = 0; i < kSortItems; ++i) {
-      const uint32_t idx = st.beg + uint32_t(i * kSortThreads) + threadIdx.x;
-      if (idx < st.vend) atomicAdd(&h[(keys[idx] >> shift) & MASK], 1u);
+  if (sort_tile<ITEMS>(vstart, views, count, cap, overflow, tb, st)) {
+#pragma unroll
+    for (int i = 0; i < ITEMS; ++i) {
+      const uint32_t idx = st.beg + uint32_t(i * kSortThreads + t);
+      if (idx < st.vend) atomicAdd(&h[(keys[idx] >> shift) & (kSortDigits - 1)], 1u);
     }
   }
   __syncthreads();
-  for (int d = threadIdx.x; d < D; d += kSortThreads) hist[int64_t(d) * nblk + tb] = h[d];
+  if (t < kSortDigits) hist[FOLD ? int64_t(tb) * kSortDigits + t : int64_t(t) * nblk + tb] = h[t];
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_radix_rowscan(uint32_t* hist, int nblk, uint32_t* digit_tot) {
-  __shared__ uint32_t red[kSortThreads / 64];
+__global__ __launch_bounds__(256) void k_radix_rowscan(uint32_t* hist, int nblk, uint32_t* digit_tot) {
+  __shared__ uint32_t red[4];
   __shared__ uint32_t carry;
   uint32_t* row = hist + int64_t(blockIdx.x) * nblk;
   if (threadIdx.x == 0) carry = 0;
   __syncthreads();
-  for (int start = 0; start < nblk; start += kSortThreads) {
+  for (int start = 0; start < nblk; start += 256) {
     const int i = start + threadIdx.x;
     const uint32_t v = i < nblk ? row[i] : 0u;
     const uint32_t ex = block_exclusive_scan_u32(v, red);
     const uint32_t c = carry;
     if (i < nblk) row[i] = c + ex;
     __syncthreads();
-    if (threadIdx.x == kSortThreads - 1) carry = c + ex + v;
+    if (threadIdx.x == 255) carry = c + ex + v;
     __syncthreads();
   }
   if (threadIdx.x == 0) digit_tot[blockIdx.x] = carry;
 }
 
-template <int BITS>
+// Ranks a wavefront's 64 ITEMS keys within their digits, in order (row r of 64 keys at a time):
+// rank[r], and in cnt (the wavefront's own counters) its keys of each digit.
+template <int ITEMS>
+__device__ __forceinline__ void wave_rank(const uint32_t (&key)[ITEMS], int shift, uint16_t* cnt,
+                                          uint16_t (&rank)[ITEMS]) {
+  const int lane = threadIdx.x & 63;
+  for (int i = lane; i < kSortDigits / 2; i += 64) reinterpret_cast<uint32_t*>(cnt)[i] = 0u;
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t d = (key[r] >> shift) & (kSortDigits - 1);
+    uint32_t lo = ~0u, hi = ~0u;  // the lanes with this lane's digit
+#pragma unroll
+    for (int bit = 0; bit < kSortBits; ++bit) {
+      const uint64_t m = __ballot((d >> bit) & 1u);
+      const uint32_t other = ((d >> bit) & 1u) - 1u;  // all bits where the lane's own bit is clear
+      lo &= uint32_t(m) ^ other;
+      hi &= uint32_t(m >> 32) ^ other;
+    }
+    const uint32_t in = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
+    const uint32_t prior = cnt[d];
+    rank[r] = uint16_t(prior + in);
+    __builtin_amdgcn_wave_barrier();
+    if (in == 0) cnt[d] = uint16_t(prior + __popc(lo) + __popc(hi));
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// By the first 256 threads, digit t each: the wavefronts' counters become offsets within the digit;
+// returns the tile's keys of digit t.
+__device__ __forceinline__ uint32_t digit_offsets(uint16_t (*cnt)[kSortDigits], int t) {
+  uint32_t c[kSortWaves], run = 0;
+#pragma unroll
+  for (int w = 0; w < kSortWaves; ++w) c[w] = cnt[w][t];
+#pragma unroll
+  for (int w = 0; w < kSortWaves; ++w) {
+    cnt[w][t] = uint16_t(run);
+    run += c[w];
+  }
+  return run;
+}
+
+// Exclusive scans over the 256 digits of two values of the first 256 threads (called by all;
+// red: 8 words; one barrier inside).
+__device__ __forceinline__ void digit_scan2(uint32_t a, uint32_t b, uint32_t* red, uint32_t& ea, uint32_t& eb) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t ia = a, ib = b;
+  if (w < kSortDigits / 64) {  // wave-uniform
+    ia = wave_add_scan(a);
+    ib = wave_add_scan(b);
+    if (lane == 63) {
+      red[w] = ia;
+      red[4 + w] = ib;
+    }
+  }
+  __syncthreads();
+  if (w < kSortDigits / 64)
+    for (int i = 0; i < w; ++i) {
+      ia += red[i];
+      ib += red[4 + i];
+    }
+  ea = ia - a;
+  eb = ib - b;
+}
+
+template <int ITEMS, bool FOLD>
 __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t* kin, const uint32_t* vin,
                                                                 uint32_t* kout, uint32_t* vout,
                                                                 const uint32_t* vstart, int views,
@@ -850,95 +955,136 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_scatter(const uint32_t* 
                                                                 const uint32_t* overflow, int shift,
                                                                 const uint32_t* hist, const uint32_t* digit_tot,
                                                                 int nblk) {
-  constexpr int D = 1 << BITS;
-  constexpr int DPT = D / kSortThreads;  // digits per thread
-  constexpr int NW = kSortThreads / 64;
-  constexpr uint32_t MASK = D - 1;
-  static_assert(D % kSortThreads == 0, "whole digits per thread");
-  // bases and per-wavefront counters are double buffered so each round needs two barriers;
-  // a round's counts and offsets are below kSortThreads, so 16 bits hold them
-  __shared__ uint32_t base[2][D];
-  __shared__ uint16_t wcnt[2][NW][D];
-  __shared__ uint32_t red[NW];
+  __shared__ uint16_t cnt[kSortWaves][kSortDigits];
+  constexpr int kTile = ITEMS * kSortThreads;
+  __shared__ uint32_t s_key[kTile], s_val[kTile];
+  __shared__ uint32_t lbase[kSortDigits], delta[kSortDigits], red[8];
+  constexpr int G = kSortThreads / kSortDigits;  // FOLD: threads that add up one digit's histograms
+  static_assert(kTile >= G * kSortDigits, "s_key and s_val hold the partial sums first");
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int tb = xcd_block(blockIdx.x, gridDim.x);  // this block's tile of keys
   if (tb >= nblk) return;                            // block-uniform
   SortTile st;
-  if (!sort_tile(vstart, views, count, cap, overflow, tb, st)) return;  // block-uniform
-  // first slot of each digit: thread t scans the view's digits t * DPT .. t * DPT + DPT - 1
-  {
-    uint32_t tot[DPT], at[DPT], sum = 0;
+  if (!sort_tile<ITEMS>(vstart, views, count, cap, overflow, tb, st)) return;  // block-uniform
+  // the keys past the view's end are all bits: last in the tile, and not written
+  uint32_t key[ITEMS], val[ITEMS];
+  const uint32_t first = st.beg + uint32_t(w * 64 * ITEMS + lane);
 #pragma unroll
-    for (int j = 0; j < DPT; ++j) {
-      const int d = t * DPT + j;
-      const uint32_t* row = hist + int64_t(d) * nblk;
-      const uint32_t first = row[st.t0];
-      tot[j] = (st.t1 < nblk ? row[st.t1] : digit_tot[d]) - first;
-      at[j] = row[tb] - first;
-      sum += tot[j];
-    }
-    uint32_t run = st.vbeg + block_exclusive_scan_u32(sum, red);
-#pragma unroll
-    for (int j = 0; j < DPT; ++j) {
-      base[0][t * DPT + j] = run + at[j];
-      run += tot[j];
-    }
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t idx = first + uint32_t(64 * r);
+    key[r] = idx < st.vend ? kin[idx] : ~0u;
+    val[r] = idx < st.vend ? vin[idx] : 0u;
   }
-  // the per-round work below takes digits t + kSortThreads j (consecutive lanes, banks)
-#pragma unroll
-  for (int j = 0; j < DPT; ++j)
-#pragma unroll
-    for (int i = 0; i < NW; ++i) {
-      wcnt[0][i][t + kSortThreads * j] = 0;
-      wcnt[1][i][t + kSortThreads * j] = 0;
+  // the view's keys of each digit, and those of its tiles in front
+  uint32_t tot = 0, pre = 0;
+  if (FOLD) {
+    const uint32_t* h = hist + (t & (kSortDigits - 1));
+#pragma unroll 8
+    for (int i = st.t0 + t / kSortDigits; i < st.t1; i += G) {
+      const uint32_t c = h[int64_t(i) * kSortDigits];
+      tot += c;
+      pre += i < tb ? c : 0u;
     }
+    s_key[t] = tot;
+    s_val[t] = pre;
+  } else if (t < kSortDigits) {
+    const uint32_t* row = hist + int64_t(t) * nblk;
+    const uint32_t before = row[st.t0];
+    tot = (st.t1 < nblk ? row[st.t1] : digit_tot[t]) - before;
+    pre = row[tb] - before;
+  }
+  uint16_t rank[ITEMS];
+  wave_rank(key, shift, cnt[w], rank);
   __syncthreads();
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
-  // every round's key and value loaded up front (one memory latency per block, not one
-  // per round)
-  uint32_t kk[kSortItems], vv[kSortItems];
+  uint32_t own = 0;
+  if (t < kSortDigits) {
+    if (FOLD)
 #pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const uint32_t idx = st.beg + uint32_t(r * kSortThreads + t);
-    kk[r] = idx < st.vend ? kin[idx] : 0u;
-    vv[r] = idx < st.vend ? vin[idx] : 0u;
-  }
-#pragma unroll
-  for (int r = 0; r < kSortItems; ++r) {
-    const int b = r & 1;
-    const bool valid = st.beg + uint32_t(r * kSortThreads + t) < st.vend;
-    const uint32_t key = kk[r], val = vv[r];
-    const uint32_t d = valid ? (key >> shift) & MASK : 0u;
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int bit = 0; bit < BITS; ++bit) {
-      const bool on = (d >> bit) & 1u;
-      const uint64_t m = __ballot(on);
-      peers &= on ? m : ~m;
-    }
-    const uint32_t rank = __popcll(peers & lt_mask);
-    if (valid && rank == 0) wcnt[b][w][d] = uint16_t(__popcll(peers));
-    __syncthreads();
-    // per digit: offsets of the four wavefronts, next round's base, clear next round's counters
-#pragma unroll
-    for (int j = 0; j < DPT; ++j) {
-      const int dd = t + kSortThreads * j;
-      uint32_t run = 0;
-#pragma unroll
-      for (int i = 0; i < NW; ++i) {
-        const uint32_t c = wcnt[b][i][dd];
-        wcnt[b][i][dd] = uint16_t(run);
-        run += c;
-        wcnt[b ^ 1][i][dd] = 0;
+      for (int i = 1; i < G; ++i) {
+        tot += s_key[i * kSortDigits + t];
+        pre += s_val[i * kSortDigits + t];
       }
-      base[b ^ 1][dd] = base[b][dd] + run;
+    own = digit_offsets(cnt, t);
+  }
+  uint32_t slot, at;
+  digit_scan2(tot, own, red, slot, at);
+  if (t < kSortDigits) {
+    lbase[t] = at;
+    delta[t] = st.vbeg + slot + pre - at;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t d = (key[r] >> shift) & (kSortDigits - 1);
+    const uint32_t i = lbase[d] + cnt[w][d] + rank[r];
+    s_key[i] = key[r];
+    s_val[i] = val[r];
+  }
+  __syncthreads();
+  const uint32_t n = min(st.vend - st.beg, uint32_t(kTile));
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t i = uint32_t(r * kSortThreads + t);
+    if (i < n) {
+      const uint32_t k = s_key[i];
+      const uint32_t dst = delta[(k >> shift) & (kSortDigits - 1)] + i;
+      kout[dst] = k;
+      vout[dst] = s_val[i];
+    }
+  }
+}
+
+// The whole sort of one view per block, in place: views of at most ITEMS kSortThreads keys.
+template <int ITEMS>
+__global__ __launch_bounds__(kSortThreads) void k_sort_small(uint32_t* keys, uint32_t* vals, const uint32_t* vstart,
+                                                             const unsigned long long* count, int64_t cap,
+                                                             const uint32_t* overflow, int passes) {
+  __shared__ uint16_t cnt[kSortWaves][kSortDigits];
+  __shared__ uint32_t s_key[ITEMS * kSortThreads], s_val[ITEMS * kSortThreads];
+  __shared__ uint32_t lbase[kSortDigits], red[8];
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const uint32_t v0 = vstart[blockIdx.x], v1 = vstart[blockIdx.x + 1];
+  const uint32_t M = clamp_count(count, cap, overflow);
+  const uint32_t beg = min(v0, M);
+  const uint32_t n = min(min(v1, M) - beg, uint32_t(ITEMS * kSortThreads));
+  if (n <= 1) return;  // block-uniform
+  // the keys past the end are all bits: they stay last, and are not written
+  uint32_t key[ITEMS], val[ITEMS];
+  const uint32_t first = uint32_t(w * 64 * ITEMS + lane);
+#pragma unroll
+  for (int r = 0; r < ITEMS; ++r) {
+    const uint32_t i = first + uint32_t(64 * r);
+    key[r] = i < n ? keys[beg + i] : ~0u;
+    val[r] = i < n ? vals[beg + i] : 0u;
+  }
+  for (int p = 0; p < passes; ++p) {
+    const int shift = p * kSortBits;
+    uint16_t rank[ITEMS];
+    wave_rank(key, shift, cnt[w], rank);
+    __syncthreads();  // (and the reads of s_key, s_val below are done)
+    const uint32_t own = t < kSortDigits ? digit_offsets(cnt, t) : 0u;
+    uint32_t at, unused;
+    digit_scan2(own, 0u, red, at, unused);
+    if (t < kSortDigits) lbase[t] = at;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      const uint32_t d = (key[r] >> shift) & (kSortDigits - 1);
+      const uint32_t i = lbase[d] + cnt[w][d] + rank[r];
+      s_key[i] = key[r];
+      s_val[i] = val[r];
     }
     __syncthreads();
-    if (valid) {
-      const uint32_t dst = base[b][d] + wcnt[b][w][d] + rank;
-      kout[dst] = key;
-      vout[dst] = val;
+    if (p + 1 == passes) break;
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+      key[r] = s_key[first + uint32_t(64 * r)];
+      val[r] = s_val[first + uint32_t(64 * r)];
     }
+  }
+  for (uint32_t i = t; i < n; i += kSortThreads) {
+    keys[beg + i] = s_key[i];
+    vals[beg + i] = s_val[i];
   }
 }
 
@@ -2666,29 +2812,29 @@ hipError_t launch_compact(int64_t n, int views, const Records& rec, const uint2*
   return hipGetLastError();
 }
 
-template <int BITS>
+template <int ITEMS, bool FOLD>
 static void radix_pass(const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout, uint32_t* hist,
-                       uint32_t* digit_tot, const uint32_t* vstart, int views, const unsigned long long* count, int64_t cap, const uint32_t* overflow,
-                       int shift, int nblk, hipStream_t s, Timer* tm) {
+                       uint32_t* digit_tot, const uint32_t* vstart, int views, const unsigned long long* count,
+                       int64_t cap, const uint32_t* overflow, int shift, int nblk, hipStream_t s, Timer* tm) {
   if (tm) tm->begin(K_RADIX_HIST);
-  k_radix_hist<BITS><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, vstart, views, count, cap, overflow, shift, hist,
-                                                                 nblk);
+  k_radix_hist<ITEMS, FOLD><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, vstart, views, count, cap, overflow, shift, hist, nblk);
   if (tm) tm->end(K_RADIX_HIST);
-  if (tm) tm->begin(K_RADIX_ROWSCAN);
-  k_radix_rowscan<<<1 << BITS, kSortThreads, 0, s>>>(hist, nblk, digit_tot);
-  if (tm) tm->end(K_RADIX_ROWSCAN);
+  if (!FOLD) {
+    if (tm) tm->begin(K_RADIX_ROWSCAN);
+    k_radix_rowscan<<<kSortDigits, 256, 0, s>>>(hist, nblk, digit_tot);
+    if (tm) tm->end(K_RADIX_ROWSCAN);
+  }
   if (tm) tm->begin(K_RADIX_SCATTER);
-  k_radix_scatter<BITS><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, vin, kout, vout, vstart, views, count, cap, overflow,
-                                                                    shift, hist, digit_tot, nblk);
+  k_radix_scatter<ITEMS, FOLD><<<xcd_grid(nblk), kSortThreads, 0, s>>>(kin, vin, kout, vout, vstart, views, count, cap, overflow,
+                                                               shift, hist, digit_tot, nblk);
   if (tm) tm->end(K_RADIX_SCATTER);
 }
 
-// key tiles of at most cap keys: whole ones, and a partial one per view
-static int64_t sort_tiles(int64_t cap, int views) { return cap / kSortTile + views; }
-int64_t radix_hist_words(int64_t cap, int views) { return sort_tiles(cap, views) << kSortBits; }
+static int64_t sort_tiles(int64_t cap, int views, int items) { return cap / (items * kSortThreads) + views; }
+int64_t radix_hist_words(int64_t cap, int views) { return sort_tiles(cap, views, kSortItemsFew) * kSortDigits; }
 
 hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt, uint32_t* vals_alt,
-                             uint32_t* hist, uint32_t* digit_tot, const uint32_t* vstart, int views,
+                             uint32_t* hist, uint32_t* digit_tot, const uint32_t* vstart, int views, int64_t per_view,
                              const unsigned long long* count, int64_t cap, const uint32_t* overflow, int key_bits,
                              bool* result_in_alt, int* passes, hipStream_t s, Timer* tm) {
   const int np = (key_bits + kSortBits - 1) / kSortBits;
@@ -2696,13 +2842,28 @@ hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
   *result_in_alt = false;
   if (cap <= 1 || np == 0) return hipSuccess;
   *passes = np;
-  const int nblk = int(sort_tiles(cap, views));
+  const int64_t most = std::min(cap, per_view);  // keys of a view, at most
+  if (most <= kSmallMost) {
+    if (tm) tm->begin(K_RADIX_SCATTER);
+    if (most <= 4 * kSortThreads)
+      k_sort_small<4><<<views, kSortThreads, 0, s>>>(keys, vals, vstart, count, cap, overflow, np);
+    else
+      k_sort_small<16><<<views, kSortThreads, 0, s>>>(keys, vals, vstart, count, cap, overflow, np);
+    if (tm) tm->end(K_RADIX_SCATTER);
+    return hipGetLastError();
+  }
+  auto folds = [&](int items) { return (most + items * kSortThreads - 1) / (items * kSortThreads) <= kSortFold; };
+  const int items = folds(kSortItemsFew) ? kSortItemsFew : kSortItems;
+  const auto pass = items == kSortItemsFew ? radix_pass<kSortItemsFew, true>
+                    : folds(kSortItems)    ? radix_pass<kSortItems, true>
+                                           : radix_pass<kSortItems, false>;
+  const int nblk = int(sort_tiles(cap, views, items));
   uint32_t* kin = keys;
   uint32_t* vin = vals;
   uint32_t* kout = keys_alt;
   uint32_t* vout = vals_alt;
   for (int p = 0; p < np; ++p) {
-    radix_pass<kSortBits>(kin, vin, kout, vout, hist, digit_tot, vstart, views, count, cap, overflow, kSortBits * p, nblk, s, tm);
+    pass(kin, vin, kout, vout, hist, digit_tot, vstart, views, count, cap, overflow, kSortBits * p, nblk, s, tm);
     std::swap(kin, kout);
     std::swap(vin, vout);
   }

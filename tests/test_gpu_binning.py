@@ -117,3 +117,23 @@ def test_allocator_that_refuses_one_large_block(R, limit, separate):
     for k in grads:
         assert float((grads[k] - grads2[k]).abs().max()) <= 1e-5 * float(grads[k].abs().max()) + 1e-20
     saved2.free()
+
+
+@pytest.mark.parametrize("views,n", [(1, 2), (1, 4096), (5, 4096), (1, 4097), (2, 16384), (1, 16385), (3, 20000),
+                                     (1, 458752), (2, 458753), (1, 917504), (2, 917505)])
+def test_depth_sort_sizes(R, views, n):
+    # sorted by one block a view up to 4,096 and 16,384 keys; by tiles of 2,048 or 4,096 keys whose
+    # histograms each block adds up, up to 224 tiles (458,752, 917,504 keys) a view; row-scanned beyond.  Depths of
+    # few values, all near the same: ties keep the record order
+    base = scenes.make_cfg1().gaussians
+    rng = np.random.default_rng(n + views)
+    g = base.subset(rng.integers(0, base.n, n))
+    g.means = g.means.copy()
+    g.means[:, :2] *= 0.05
+    g.means[:, 2] = (2.0 + rng.integers(0, 700, n) * 2.0 ** -12).astype(np.float32)
+    g.scales = (g.scales * 0.02).astype(np.float32)
+    f = 60.0
+    cams = [scenes.Camera(64 - 8 * k, 48, f, f, 32.0 - 8 * k, 24.0, np.eye(3, dtype=np.float32),
+                          np.zeros(3, np.float32)) for k in range(views)]
+    say("depth sort", views, n)
+    _keys(R, g, cams, settings(tile=16))
