@@ -25,6 +25,7 @@ struct gsr_ctx {
   gsr_alloc alloc{};  // the caller's allocator; alloc.alloc == nullptr: the stream-ordered pool
   std::string err;
   unsigned long long* h_total = nullptr;  // pinned read-back slots: pair count M, visible records
+  unsigned long long* d_h_total = nullptr;  // their device address
   Timer timer;
   void* bwd_scratch = nullptr;  // the eager backward's 2D-gradient rows, kept between calls (grow-only)
   size_t bwd_scratch_bytes = 0;
@@ -87,7 +88,7 @@ struct gsr_graph {
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   hipEvent_t done = nullptr;
-  uint32_t* h_flag = nullptr;  // pinned copy of the overflow word, written by the graph
+  uint32_t* h_flag = nullptr;  // pinned copy of the overflow word, written by the captured loss kernel
   bool launched = false;
   bool overflowed = false;
 };
@@ -365,11 +366,11 @@ const uint32_t* find_hint(gsr_ctx* ctx, const gsr_saved* sv) {
   return nullptr;
 }
 
-// Keeps this forward's per-tile work (enqueued after its compositing) as the hint for the
-// next forward over the same tiles.  Failure to keep it only loses the hint.
-void keep_hint(gsr_ctx* ctx, const gsr_saved* sv, hipStream_t s) {
+// Where this forward's compositing writes its per-tile work as the hint for the next forward
+// over the same tiles (null: nowhere; not having it only loses the hint).
+uint32_t* hint_slot(gsr_ctx* ctx, const gsr_saved* sv, hipStream_t s) {
   const int64_t T = sv->vt.total_tiles;
-  if (T == 0) return;
+  if (T == 0) return nullptr;
   const std::vector<int> g = tile_grid(sv);
   gsr_ctx::WorkHint* slot = nullptr;
   for (auto& h : ctx->hints)
@@ -393,16 +394,19 @@ void keep_hint(gsr_ctx* ctx, const gsr_saved* sv, hipStream_t s) {
     if (dev_alloc(ctx, s, &p, size_t(T) * sizeof(uint32_t)) != GSR_OK) {  // a hint is optional
       ctx->err = err;
       slot->grid.clear();
-      return;
+      return nullptr;
     }
     slot->tiles = static_cast<uint32_t*>(p);
   }
   slot->count = T;
-  if (hipMemcpyAsync(slot->tiles, sv->ck.tile_nmax, size_t(T) * sizeof(uint32_t), hipMemcpyDeviceToDevice, s) !=
-      hipSuccess) {
-    (void)hipGetLastError();
-    slot->grid.clear();
-  }
+  return slot->tiles;
+}
+
+// Forgets the hint of this forward's tiles (its compositing was not enqueued).
+void drop_hint(gsr_ctx* ctx, const gsr_saved* sv) {
+  const std::vector<int> g = tile_grid(sv);
+  for (auto& h : ctx->hints)
+    if (h.grid == g) h.grid.clear();
 }
 
 // Whether the compaction scans the projection's block sums itself (see launch_compact).
@@ -424,7 +428,8 @@ hipError_t enqueue_project(gsr_saved* sv, hipStream_t s, bool timing) {
   // a captured step with few block sums leaves their scan to the compaction (the host
   // does not read the totals); an eager forward reads them to size its buffers
   if (e == hipSuccess && !raw_sums(sv))
-    e = T(K_SCAN, [&] { return launch_scan_pairs(sv->blocksums, int64_t(sv->V) * sv->nblk, sv->d_total, s); });
+    e = T(K_SCAN, [&] { return launch_scan_pairs(sv->blocksums, int64_t(sv->V) * sv->nblk, sv->d_total,
+                                                  sv->graph ? nullptr : ctx->d_h_total, s); });
   return e;
 }
 
@@ -581,8 +586,7 @@ gsr_status forward_eager(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_camera*
   hipError_t e = enqueue_project(sv, strm, true);
   int64_t M = 0, NV = 0;
   if (e == hipSuccess && g->n > 0) {
-    e = hipMemcpyAsync(ctx->h_total, sv->d_total, 2 * sizeof(unsigned long long), hipMemcpyDeviceToHost, strm);
-    if (e == hipSuccess) e = hipStreamSynchronize(strm);
+    e = hipStreamSynchronize(strm);  // (the scan wrote the totals to pinned memory)
     M = int64_t(ctx->h_total[0]);
     NV = int64_t(ctx->h_total[1]);
   }
@@ -601,12 +605,14 @@ gsr_status forward_eager(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_camera*
     return st;
   }
   sv->order_hint = find_hint(ctx, sv);
+  sv->ck.tile_hint = hint_slot(ctx, sv, strm);
   e = enqueue_sort_blend(sv, strm, true);
+  sv->ck.tile_hint = nullptr;
   if (e != hipSuccess) {
+    drop_hint(ctx, sv);
     release(sv);
     return fail(ctx, GSR_EDEVICE, std::string("forward (sort/blend) failed: ") + hipGetErrorString(e));
   }
-  keep_hint(ctx, sv, strm);
   // keep the pair list, return every temporary to the pool
   free_list(sv, sv->temps);
   *out = sv;
@@ -691,6 +697,12 @@ gsr_status gsr_ctx_create(int32_t device, void* hip_stream, const gsr_alloc* all
       hipSuccess) {
     delete c;
     return fail(nullptr, GSR_ENOMEM, "pinned host allocation failed");
+  }
+  if (hipHostGetDevicePointer(reinterpret_cast<void**>(&c->d_h_total), c->h_total, 0) != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipHostFree(c->h_total);
+    delete c;
+    return fail(nullptr, GSR_EDEVICE, "pinned host memory has no device address");
   }
   // keep freed pool memory cached: the per-step allocations are then served without the driver
   hipMemPool_t pool;
@@ -1050,6 +1062,8 @@ gsr_status gsr_graph_create(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_came
   }
 
   hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&gr->h_flag), sizeof(uint32_t), hipHostMallocDefault);
+  uint32_t* d_flag = nullptr;
+  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&d_flag), gr->h_flag, 0);
   // every control word starts at zero once; the steps clear only their own words
   if (e == hipSuccess) e = launch_fill_u32(sv->ctrl, 0u, kCtrlWords, ctx->stream);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&gr->done, hipEventDisableTiming);
@@ -1068,11 +1082,10 @@ gsr_status gsr_graph_create(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_came
     // the loss kernel also lists the backward's work items; the loss total is added up by
     // the backward projection
     if (k == hipSuccess)
-      k = launch_loss_l1(lvt, depth_weight, sv->loss_part, nullptr, cs, sv->order, sv->s.batch, &sv->ck, sv->ctrl);
+      k = launch_loss_l1(lvt, depth_weight, sv->loss_part, nullptr, cs, sv->order, sv->s.batch, &sv->ck, sv->ctrl,
+                         d_flag);
     if (k == hipSuccess)
       k = enqueue_backward(sv, bvt, sv->grad2d, go, cs, false, ad, opt ? opt->state : nullptr, loss_dev);
-    if (k == hipSuccess)
-      k = hipMemcpyAsync(gr->h_flag, sv->ctrl + kOverflowSticky, sizeof(uint32_t), hipMemcpyDeviceToHost, cs);
     e = hipStreamEndCapture(cs, &gr->graph);
     if (k != hipSuccess) e = k;
   }

@@ -200,6 +200,7 @@ struct Ckpt {
   float* state;         // [tiles][kmax][5][pixels of a tile]: T, colour (3), depth in front
   float4* acc;          // [pixels] colour (3) and depth accumulated, without background
   uint32_t* tile_nmax;  // [tiles] longest contributor list of the tile
+  uint32_t* tile_hint;  // the forward's copy of tile_nmax for the context's next forward, or null
   uint32_t* slice_items;  // [tiles / 256, rounded up] items of each 256 tiles of the queue
   uint2* items;         // [cap_items] backward work items (tile, first batch)
   int32_t kmax;         // checkpoints per tile
@@ -289,9 +290,10 @@ hipError_t launch_project(int deg, const GaussDev& g, const ViewTable& vt, const
                           const Records& rec, uint2* blocksums, int nblk, float* zero_rows, uint32_t* ctrl,
                           int clear_words, float exact_k, hipStream_t s);
 // Scans the projection's count block sums (an array of scan_pairs_words(count) pairs) for the
-// compaction and writes the totals.
+// compaction and writes the totals, also to host (a device address of pinned memory) if not null.
 int64_t scan_pairs_words(int64_t count);
-hipError_t launch_scan_pairs(uint2* blocksums, int64_t count, unsigned long long* totals, hipStream_t s);
+hipError_t launch_scan_pairs(uint2* blocksums, int64_t count, unsigned long long* totals, unsigned long long* host,
+                             hipStream_t s);
 // raw: blocksums as the projection wrote them (not scanned; allowed where compact_scans),
 // and the compaction writes totals[0..1] itself; else scanned by launch_scan_pairs,
 // which wrote the totals.  vstart gets views + 1 words: where each view's records start.
@@ -337,7 +339,7 @@ int loss_partials(const ViewTable& vt);  // block partial sums launch_loss_l1 wr
 // control words ctrl), so that launch_blend_bwd can skip its own listing.
 hipError_t launch_loss_l1(const ViewTable& vt, float depth_w, float* part, float* loss, hipStream_t s,
                           const uint32_t* order = nullptr, int batch = 0, const Ckpt* ck = nullptr,
-                          uint32_t* ctrl = nullptr);
+                          uint32_t* ctrl = nullptr, uint32_t* host_flag = nullptr);
 // Lists the backward's (tile, stride) work items unless items_listed (the loss kernel
 // did), then runs them.
 hipError_t launch_blend_bwd(int tile, int batch, const ViewTable& vt, const Rules& ru, const Records& rec,

@@ -599,7 +599,21 @@ __device__ __forceinline__ unsigned long long block_inclusive_scan_u64(unsigned 
   return part[t];
 }
 
-__global__ __launch_bounds__(1024) void k_scan_pairs(uint2* a, int count, unsigned long long* totals) {
+// Writes the totals, and to the host's pinned copy where there is one (read after a
+// synchronisation of the stream; a copy of the two words took the host and the stream longer than
+// the scan).
+__device__ __forceinline__ void store_totals(unsigned long long x, unsigned long long y, unsigned long long* totals,
+                                             unsigned long long* host) {
+  totals[0] = x;
+  totals[1] = y;
+  if (host) {
+    __hip_atomic_store(host, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __hip_atomic_store(host + 1, y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+__global__ __launch_bounds__(1024) void k_scan_pairs(uint2* a, int count, unsigned long long* totals,
+                                                     unsigned long long* host) {
   __shared__ unsigned long long part[1024];
   const int t = threadIdx.x;
   const int per = (count + 1023) / 1024;
@@ -620,10 +634,7 @@ __global__ __launch_bounds__(1024) void k_scan_pairs(uint2* a, int count, unsign
     rx += x.x;
     ry += x.y;
   }
-  if (t == 1023) {
-    totals[0] = ix;
-    totals[1] = iy;
-  }
+  if (t == 1023) store_totals(ix, iy, totals, host);
 }
 
 __global__ __launch_bounds__(1024) void k_scan_u32(uint32_t* a, int count, unsigned long long* total) {
@@ -659,7 +670,7 @@ __global__ __launch_bounds__(kSumTile) void k_sum_pairs(const uint2* a, int64_t 
 }
 
 __global__ __launch_bounds__(kSumTile) void k_scan_pairs_down(uint2* a, int64_t count, const uint2* part,
-                                                              unsigned long long* totals) {
+                                                              unsigned long long* totals, unsigned long long* host) {
   __shared__ unsigned long long red[kSumTile];
   const int t = threadIdx.x;
   unsigned long long bx = 0, by = 0;
@@ -680,10 +691,7 @@ __global__ __launch_bounds__(kSumTile) void k_scan_pairs_down(uint2* a, int64_t 
   __syncthreads();
   const unsigned long long iy = y0 + block_inclusive_scan_u64<kSumTile>(v.y, red);
   if (i < count) a[i] = make_uint2(uint32_t(ix - v.x), uint32_t(iy - v.y));
-  if (i == count - 1) {
-    totals[0] = ix;
-    totals[1] = iy;
-  }
+  if (i == count - 1) store_totals(ix, iy, totals, host);
 }
 
 // Flags a capacity overflow: the step's word and the sticky copy next to it.
@@ -1921,7 +1929,10 @@ __global__ __launch_bounds__(TS* TS) void k_blend_fwd(ViewTable vt, Rules ru, Re
     __syncthreads();
     if ((threadIdx.x & 63) == 0) atomicMax(&s_nmax, wl);
     __syncthreads();
-    if (threadIdx.x == 0) ck.tile_nmax[tile] = s_nmax;
+    if (threadIdx.x == 0) {
+      ck.tile_nmax[tile] = s_nmax;
+      if (ck.tile_hint) ck.tile_hint[tile] = s_nmax;
+    }
   }
 }
 
@@ -2009,13 +2020,16 @@ __global__ __launch_bounds__(256) void k_bwd_items(const uint32_t* order, int to
 // ------------------------------------------------------------------------------------
 // K7: L1 loss and its gradient with respect to the rendered colour and depth
 // ------------------------------------------------------------------------------------
-// With order non-null (a captured step) the first blocks also list the backward's work
+// host_flag (a captured step's, else null): the host's pinned copy of the sticky overflow word, which
+// nothing after the forward raises.  With order non-null (a captured step) the first blocks also list the backward's work
 // items (list_bwd_items) for the tiles the forward just composited.
 __global__ __launch_bounds__(256) void k_loss_l1(ViewTable vt, float depth_w, float* partial, const uint32_t* order,
-                                                int total_tiles, int stride, Ckpt ck, uint32_t* ctrl) {
+                                                int total_tiles, int stride, Ckpt ck, uint32_t* ctrl, uint32_t* host_flag) {
   __shared__ float red[4];
   __shared__ uint32_t ired[4];
   const ViewDev& cam = vt.v[blockIdx.y];
+  if (host_flag && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    __hip_atomic_store(host_flag, ctrl[kOverflowSticky], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   if (order)  // (block-uniform; more slices than blocks where tiles are few pixels)
     for (int b = int(blockIdx.y * gridDim.x + blockIdx.x); b * 256 < total_tiles; b += int(gridDim.x * gridDim.y)) {
       list_bwd_items(b, order, total_tiles, stride, ck, ctrl, ired);
@@ -2789,13 +2803,14 @@ hipError_t launch_scan_small(uint32_t* a, int count, unsigned long long* total, 
 
 int64_t scan_pairs_words(int64_t count) { return count + (count > kSumMany ? (count + kSumTile - 1) / kSumTile : 0); }
 
-hipError_t launch_scan_pairs(uint2* blocksums, int64_t count, unsigned long long* totals, hipStream_t s) {
+hipError_t launch_scan_pairs(uint2* blocksums, int64_t count, unsigned long long* totals, unsigned long long* host,
+                             hipStream_t s) {
   if (count > kSumMany) {
     const int tiles = blocks_for(count, kSumTile);
     k_sum_pairs<<<tiles, kSumTile, 0, s>>>(blocksums, count, blocksums + count);
-    k_scan_pairs_down<<<tiles, kSumTile, 0, s>>>(blocksums, count, blocksums + count, totals);
+    k_scan_pairs_down<<<tiles, kSumTile, 0, s>>>(blocksums, count, blocksums + count, totals, host);
   } else {
-    k_scan_pairs<<<1, 1024, 0, s>>>(blocksums, int(count), totals);
+    k_scan_pairs<<<1, 1024, 0, s>>>(blocksums, int(count), totals, host);
   }
   return hipGetLastError();
 }
@@ -3052,11 +3067,11 @@ static void launch_items_sum(const ViewTable& vt, int stride, const uint32_t* or
 }
 
 hipError_t launch_loss_l1(const ViewTable& vt, float depth_w, float* part, float* loss, hipStream_t s,
-                          const uint32_t* order, int batch, const Ckpt* ck, uint32_t* ctrl) {
+                          const uint32_t* order, int batch, const Ckpt* ck, uint32_t* ctrl, uint32_t* host_flag) {
   const int np = loss_partials(vt);
   if (order) launch_items_sum(vt, ckpt_stride(batch), order, *ck, s);
   k_loss_l1<<<dim3(np / vt.nviews, vt.nviews), 256, 0, s>>>(vt, depth_w, part, order, vt.total_tiles,
-                                                            ckpt_stride(batch), ck ? *ck : Ckpt{}, ctrl);
+                                                            ckpt_stride(batch), ck ? *ck : Ckpt{}, ctrl, host_flag);
   if (loss) k_loss_sum<<<1, 256, 0, s>>>(part, np, loss);
   return hipGetLastError();
 }
