@@ -2973,8 +2973,12 @@ hipError_t launch_first_nonfinite(const GaussDev& g, int sh_degree, uint32_t* fi
 
 // Persistent grid: blocks resident at once, at most `cap_per_cu` per compute unit.  blend_fwd
 // runs fastest at 2 blocks per CU on one 640x480 view, where its heaviest tiles'
-// single-wavefront chains bound it and then share a SIMD with fewer others, and at 4 with
-// many tiles per CU (eight views).  blend_bwd: with many items the blocks in flight hide
+// single-wavefront chains bound it and then share a SIMD with fewer others (60, 64, 70 us at 2,
+// 3, 4; tiles of 8, 321x239: 42, 47 at 2, 6), and with many tiles per CU at as many as its registers
+// allow (eight views 424, 410, 408 us at 4, 5, 6; sixteen 1752x1168 ones 6.63, 6.29, 6.15 ms; one
+// of those 365, 348, 354 us).  Tiles of 8 are one wavefront each: 316, 291, 286, 300 us at 4, 6, 12, 18
+// on 1280x960 (19k tiles), 1168, 1084, 1031, 1007 over eight views (67k), but 101, 104, 116 at 4,
+// 6, 12 on 640x480 (4,800).  blend_bwd: with many items the blocks in flight hide
 // each item's fixed latency and the more the better (tiles of 16, sixteen 1752x1168 views:
 // 18.5, 14.0, 12.7 ms at 5, 8, 10 per CU; eight uneven views 1204, 967, 930 us), while on one
 // 640x480 view 8 and 10 measure the same (128, 130 us).  Tiles of 8 hit the same few rows from
@@ -3007,7 +3011,8 @@ static int device_cus() {
   return cus;
 }
 constexpr int kFwdBlocksPerCU = 2;        // up to kFwdManyTilesPerCU tiles per CU
-constexpr int kFwdBlocksPerCUMany = 4;    // beyond
+constexpr int kFwdBlocksPerCUMany = 6;    // beyond
+constexpr int kFwd8BlocksPerCUMany = 12;  // tiles of 8 beyond 4 kFwdManyTilesPerCU tiles per CU
 constexpr int kFwdManyTilesPerCU = 16;
 constexpr int kBwdBlocksPerCU = 5;        // tiles of 8 (one wavefront a block)
 constexpr int kBwdBlocksPerCUMany = 20;   // beyond 4 kFwdManyTilesPerCU tiles per CU
@@ -3018,7 +3023,10 @@ template <int TS, int BATCH>
 static void blend_fwd_t(const ViewTable& vt, const Rules& ru, const Records& rec, const uint2* ranges,
                         const uint32_t* vals, float* T_final, uint32_t* n_contrib, const TileQueue& q,
                         const Ckpt& ck, hipStream_t s) {
-  const int cap = vt.total_tiles > kFwdManyTilesPerCU * device_cus() ? kFwdBlocksPerCUMany : kFwdBlocksPerCU;
+  const int many = kFwdManyTilesPerCU * device_cus();
+  const int cap = TS == 8 && vt.total_tiles > 4 * many ? kFwd8BlocksPerCUMany
+                  : vt.total_tiles > many              ? kFwdBlocksPerCUMany
+                                                       : kFwdBlocksPerCU;
   const int grid = std::min(vt.total_tiles, resident_blocks<k_blend_fwd<TS, BATCH>>(TS * TS, cap));
   k_blend_fwd<TS, BATCH><<<grid, TS * TS, 0, s>>>(vt, ru, rec, ranges, vals, T_final, n_contrib, q, ck);
 }
