@@ -6,7 +6,7 @@
 //                     already present costs one load); stamp the block's slot with the frame
 //   k_tsdf_assign     one thread per table slot: give new keys a pool index (one counter
 //                     atomic per wavefront with new keys, no thread waits on another)
-//   k_tsdf_integrate  a 512-thread block per 128 table slots, one thread per voxel of
+//   k_tsdf_integrate  a 512-thread block per 64 to 512 table slots, one thread per voxel of
 //                     each map block stamped with this frame: project the voxel centre, read
 //                     the nearest pixel's depth, and apply Eq. 6-9 to the voxel's distance
 //                     and weight (coalesced, HBM bound)
@@ -102,35 +102,43 @@ __global__ __launch_bounds__(256) void k_tsdf_assign(TsdfDev m) {
   }
 }
 
-// One 512-thread block per kSlotsPerBlock table slots: a thread reads a slot's stamp
+// One 512-thread block per `slots` table slots (64 to kMostSlots): a thread reads a slot's stamp
 // and pool index, the block gathers the slots stamped with this frame into LDS (ballot
 // ranks and a prefix over the wavefronts) with their coordinates, then every thread
 // updates its voxel of each gathered block.  The number of met blocks is added once per block.
-// The updates of one block are a chain of dependent loads, so slots are few enough that every CU
-// holds several blocks: a 640x480 frame took 50 us at 512 slots, 34 at 256, 33 at 128, 36 at 64.
-constexpr int kSlotsPerBlock = 128;
+// The updates of one block are a chain of dependent loads and a block without any costs its launch,
+// so a table is cut into about kFuseBlocks blocks, four per CU: a 640x480 frame took 50, 34, 33, 36 us
+// at 512, 256, 128, 64 slots of a table of 2^17, and 31 and 51 at 512 and 128 of one of 2^19.
+constexpr int kMostSlots = kBlockVoxels;
+constexpr uint64_t kFuseBlocks = 1024;
+
+static int fuse_slots(uint64_t table) {
+  uint64_t n = 64;
+  while (n < uint64_t(kMostSlots) && n * kFuseBlocks < table) n *= 2;
+  return int(n);
+}
 
 __global__ __launch_bounds__(kBlockVoxels) void k_tsdf_integrate(const float* depth, TsdfCam cam, TsdfDev m,
-                                                                 TsdfRules ru, uint32_t frame) {
+                                                                 TsdfRules ru, uint32_t frame, int slots) {
 #pragma clang fp contract(off)
-  __shared__ uint32_t s_blk[kSlotsPerBlock];
-  __shared__ int4 s_crd[kSlotsPerBlock];
-  __shared__ uint32_t s_cnt[kSlotsPerBlock / 64];
+  __shared__ uint32_t s_blk[kMostSlots];
+  __shared__ int4 s_crd[kMostSlots];
+  __shared__ uint32_t s_cnt[kMostSlots / 64];
   const int t = threadIdx.x;
   const int lane = t & 63, wv = t >> 6;
-  const uint32_t h = blockIdx.x * uint32_t(kSlotsPerBlock) + uint32_t(t);
+  const uint32_t h = blockIdx.x * uint32_t(slots) + uint32_t(t);
   bool met = false;
   uint32_t b = kUnassigned;
-  if (t < kSlotsPerBlock && h <= m.slot_mask && m.stamp[h] == frame) {
+  if (t < slots && h <= m.slot_mask && m.stamp[h] == frame) {
     b = m.vals[h];
     met = b < m.cap_blocks;  // a block without a pool index (pool full) is skipped
   }
   const uint64_t mask = __ballot(met);
-  if (t < kSlotsPerBlock && lane == 0) s_cnt[wv] = uint32_t(__popcll(mask));
+  if (lane == 0) s_cnt[wv] = uint32_t(__popcll(mask));
   __syncthreads();
   uint32_t before = 0, total = 0;
 #pragma unroll
-  for (int i = 0; i < kSlotsPerBlock / 64; ++i) {
+  for (int i = 0; i < kMostSlots / 64; ++i) {
     before += i < wv ? s_cnt[i] : 0u;
     total += s_cnt[i];
   }
@@ -198,8 +206,9 @@ hipError_t launch_tsdf_alloc(const float* depth, const TsdfCam& cam, const TsdfD
 
 hipError_t launch_tsdf_fuse(const float* depth, const TsdfCam& cam, const TsdfDev& m, const TsdfRules& ru,
                             uint32_t frame, hipStream_t s) {
-  k_tsdf_integrate<<<unsigned((uint64_t(m.slot_mask) + kSlotsPerBlock) / kSlotsPerBlock), kBlockVoxels, 0, s>>>(
-      depth, cam, m, ru, frame);
+  const int slots = fuse_slots(uint64_t(m.slot_mask) + 1);
+  k_tsdf_integrate<<<unsigned((uint64_t(m.slot_mask) + slots) / slots), kBlockVoxels, 0, s>>>(depth, cam, m, ru, frame,
+                                                                                        slots);
   return hipGetLastError();
 }
 
