@@ -7,11 +7,11 @@
 //   K3/K4               the stable sort of the (tile id << 32 | depth bits) keys, without
 //                       materialising them: k_compact + k_radix_* sort the visible records by
 //                       depth bits (stable LSD, 8-bit digits: histogram / row scan /
-//                       ballot-multisplit scatter); k_bin_* then bin that depth order stably,
+//                       ballot-multisplit scatter; few: k_sort_small); k_bin_* then bin that depth order stably,
 //                       first into tile rows, then into the tiles of each row, so every
 //                       tile receives its records in ascending (depth, record) order
-//   K5                  the tile ranges come from the binning's scan (k_bin_ranges);
-//                       k_tile_order queues the tiles heaviest first
+//   K5                  the tile ranges come from the binning's scan (tile_range); the tile
+//                       stage, or k_tile_order, queues the tiles heaviest first
 //   K6 k_blend_fwd      per tile: front-to-back compositing, Eq. 11 with clamp/skip/stop
 //   K7 k_loss_l1        Eq. 12 (mean L1 colour) + weighted mean L1 depth, its gradient
 //   K8 k_blend_bwd2     per (tile, stride) item, back to front: transmittance recovered by
