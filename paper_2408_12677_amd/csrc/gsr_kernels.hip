@@ -384,13 +384,6 @@ __device__ __forceinline__ void stage_record(const Records& rec, uint32_t id, fl
   col = make_float4(c.x, c.y, c.z, g1.z);
 }
 
-// Whether the alpha of a staged splat (a', b', c', o) is never clamped and always finite: o below
-// alpha_max by more than the rounding of exp2(q') <= 1, and a conic whose products with
-// pixel offsets (below 2^14) stay finite.  NaNs are not plain.
-__device__ __forceinline__ bool plain_splat(const float4& sq, float amax) {
-  return sq.w * 1.0001f <= amax && fabsf(sq.x) + fabsf(sq.y) + fabsf(sq.z) < 1e28f;
-}
-
 // ------------------------------------------------------------------------------------
 // Real spherical harmonics, orthonormal with Condon-Shortley phase, as Cartesian
 // polynomials of the unit direction (x, y, z).  Constants are N_l^m (and sqrt 2 for
@@ -2348,13 +2341,11 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
       const int bstart = max(lo, bend - SB);
       const int nstage = bend - bstart;
       __syncthreads();
-      int odd = 0;
       for (int j = threadIdx.x; j < nstage; j += NT) {
         const uint32_t id = vals[rg.x + bstart + j];
         float mx, my;
         float4 sq, sc;
         stage_record(rec, id, mx, my, sq, sc);
-        odd |= !plain_splat(sq, ru.amax);
         s_id[j] = id;
         s_mu[j] = make_float2(mx, my);
         s_q[j] = sq;
@@ -2363,7 +2354,7 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
         s_c[2][j] = sc.z;
         s_c[3][j] = sc.w;
       }
-      const bool plain = __syncthreads_or(odd) == 0;  // no pixel clamps a staged splat's alpha
+      __syncthreads();
       // Groups of staged entries, back to front.  First everything that does not depend on the
       // running T and B, for the whole group at once (its LDS reads and exponentials overlap);
       // g . (colour, depth) as rank-1 updates on the matrix cores (four entries each).  Then the recurrences and sums, entry by entry;
@@ -2374,8 +2365,8 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
       // The kernel is bound by VALU issue where many items are in flight, and by its items'
       // latency where few are; measured issue costs per wavefront instruction are 2 cycles for
       // adds, multiplies and fmas, 4 for compares, selects, min and DPP, 8 for exponentials,
-      // reciprocals, lane swaps and the 4x4x1 products.  Against one entry at a time, an alpha
-      // clamp on every entry and centre atomics of their own: 15.7 -> 12.9 ms over sixteen
+      // reciprocals, lane swaps and the 4x4x1 products.  Against one entry at a time and centre
+      // atomics of their own: 15.7 -> 12.9 ms over sixteen
       // 1752x1168 views, 1105 -> 925 us over eight uneven ones, 175 -> 124 us and 149 -> 122 us on
       // one 876x584 (170k splats) and one 640x480 view (500k).  Taking the sums as matrix products
       // (16x16x4, splats by pixels) was slower over many views (19.4 ms): they share the
@@ -2422,16 +2413,13 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
           float u[PPL], c0 = 0.f, c1 = 0.f, c2 = 0.f, z = 0.f;
 #pragma unroll
           for (int i = 0; i < PPL; ++i) {
-            float al, Gu;  // alpha, and dalpha/do = G (0 where clamped)
-            if (plain) {
-              Gu = act[j][i] ? G[j][i] : 0.f;
-              al = o[j] * Gu;
-            } else {
-              const float a = o[j] * G[j][i];
-              const bool below = a <= ru.amax;
-              al = act[j][i] ? (below ? a : ru.amax) : 0.f;
-              Gu = act[j][i] && below ? G[j][i] : 0.f;
-            }
+            // The clamp is tested at every pixel: an opacity below alpha_max does not rule it out, for the
+            // conic of a long thin splat comes from a det = a c - b^2 that cancels, and with it
+            // q' can come out positive (G of 1.03 at the default low-pass, over 40 without one).
+            const float a = o[j] * G[j][i];
+            const bool below = a <= ru.amax;
+            const float al = act[j][i] ? (below ? a : ru.amax) : 0.f;
+            const float Gu = act[j][i] && below ? G[j][i] : 0.f;  // dalpha/do
             const float iom = __builtin_amdgcn_rcpf(1.f - al);
             p[i].T *= iom;
             const float w = al * p[i].T;
