@@ -2377,7 +2377,7 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
         const float e0 = s_c[0][je], e1 = s_c[1][je], e2 = s_c[2][je], e3 = s_c[3][je];
         float G[GS][PPL], o[GS];  // (alpha before the clamp is o G)
         bool act[GS][PPL];
-        float dx[GS], dy0[GS];
+        float dx[GS], dy[GS][PPL];
         f32x4 S[GS / 4][PPL];
         uint32_t hits = 0;
         int lim[PPL];  // the pixels' entries of this group
@@ -2397,11 +2397,11 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
           const float4 sq = s_q[jb + j];
           const float2 mu = s_mu[jb + j];
           dx[j] = fpx - mu.x;
-          dy0[j] = p[0].fpy - mu.y;
           o[j] = sq.w;
 #pragma unroll
           for (int i = 0; i < PPL; ++i) {
-            const float a = splat_alpha(dx[j], i == 0 ? dy0[j] : p[i].fpy - mu.y, sq.x, sq.y, sq.z, sq.w, G[j][i]);
+            dy[j][i] = p[i].fpy - mu.y;
+            const float a = splat_alpha(dx[j], dy[j][i], sq.x, sq.y, sq.z, sq.w, G[j][i]);
             act[j][i] = j < lim[i] && !(a < ru.amin);
             hits |= __ballot(act[j][i]) != 0ull ? 1u << j : 0u;
           }
@@ -2431,13 +2431,14 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
             c2 += p[i].gC2 * w;
             z += p[i].gD * w;
           }
-          // the lane's moments of u over y; its second pixel is one below the first (dy + 1)
-          const float dy = dy0[j];
-          float q = u[0], qy = dy * q, qyy = dy * qy;
+          // the lane's moments of u over y, each pixel's from its own offset (taken from the first
+          // pixel's, as dy + 1, a pixel close to the splat's row leaves the rounding of larger terms)
+          float q = u[0], qy = dy[j][0] * u[0], qyy = dy[j][0] * qy;
           if constexpr (PPL == 2) {
-            q = u[0] + u[1];
-            qy = dy * q + u[1];
-            qyy = dy * (qy + u[1]) + u[1];
+            const float y1 = dy[j][1] * u[1];
+            q += u[1];
+            qyy = __builtin_fmaf(dy[j][1], y1, qyy);
+            qy += y1;
           }
           // (each bank of four lanes holds one of the sums: they store the same word)
           s_g[wv][jb + j][lane >> 2] = splat_sums(q, qy, qyy, c0, c1, c2, z, dx[j]);

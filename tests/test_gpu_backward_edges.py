@@ -7,7 +7,7 @@ import scenes
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
-from parity_util import settings, to_dev  # noqa: E402
+from parity_util import oracle_for, settings, to_dev  # noqa: E402
 from test_gpu_parity import R, run_fwd, say  # noqa: E402, F401
 
 F32 = np.float32
@@ -119,3 +119,32 @@ def test_needles_past_the_clamp(R, kind, tile):
         got = grads[k].cpu().numpy().astype(np.float64).reshape(ref[k].shape)
         ok = close(got, ref[k])
         assert ok.all(), (k, got[~ok][:4], ref[k][~ok][:4])
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+def test_second_pixel_close_to_the_centre(R, tile):
+    # one pixel a splat has a gradient: the lower one of a lane's two (tiles of 16 and 32), its centre a
+    # 256th of a pixel below the splat's.  dL/d(conic C) is then u dy^2 with dy^2 = 1.5e-5, which is
+    # lost (6e-8 of u) if it is formed from the upper pixel's offset
+    w = h = 128
+    f, z, d = 2000.0, 2.0, 2.0 ** -8
+    cam = scenes.Camera(w, h, f, f, w / 2.0, h / 2.0, I3, Z3)
+    x, y = (a.reshape(-1) for a in np.meshgrid(np.arange(9, w, 16), np.arange(9, h, 16)))
+    n = len(x)
+    means = np.stack([(x - w / 2.0) * z / f, (y - d - h / 2.0) * z / f, np.full(n, z)], 1)
+    g = scenes.random_gaussians(np.random.default_rng(5), means, 0)
+    g.scales = (z / f * np.linspace(0.5, 1.5, n)[:, None] * np.ones((1, 3))).astype(F32)
+    g.quats = np.tile([1, 0, 0, 0], (n, 1)).astype(F32)
+    g.opacities = np.linspace(0.3, 0.8, n).astype(F32)
+    s = settings(tile=tile)
+    say("moments", tile)
+    _, images, saved = run_fwd(R, g, [cam], s)
+    gc = np.zeros((3, h, w), F32)
+    gc[:, y, x] = 1.0
+    grads = R.backward(saved, [torch.from_numpy(gc).cuda()])
+    orc = oracle_for(g, [cam], s)
+    orc.forward()
+    ref = orc.backward([gc.astype(np.float64)], None, None)["scales"][:, 1]
+    got = grads["scales"].cpu().numpy().astype(np.float64)[:, 1]
+    # some forty roundings of 6e-8 between the pixel and the scale
+    np.testing.assert_allclose(got, ref, rtol=2e-5)
