@@ -2419,13 +2419,14 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
             const float a = o[j] * G[j][i];
             const bool below = a <= ru.amax;
             const float al = act[j][i] ? (below ? a : ru.amax) : 0.f;
-            const float Gu = act[j][i] && below ? G[j][i] : 0.f;  // dalpha/do
             const float iom = __builtin_amdgcn_rcpf(1.f - al);
             p[i].T *= iom;
             const float w = al * p[i].T;
             const float D = S[j / 4][i][j % 4] - p[i].B;
             p[i].B += al * D;
-            u[i] = (p[i].T * D + p[i].gATf * iom) * Gu;
+            // (selected, not multiplied by zero: a NaN or infinity in a pixel's gradient stays with the
+            // splats that the pixel takes)
+            u[i] = act[j][i] && below ? (p[i].T * D + p[i].gATf * iom) * G[j][i] : 0.f;
             c0 += p[i].gC0 * w;
             c1 += p[i].gC1 * w;
             c2 += p[i].gC2 * w;

@@ -1,4 +1,5 @@
-"""GPU backward where binary32 is strained: needles whose rounded conic is not positive definite."""
+"""GPU backward at the edges of binary32: needles whose rounded conic is not positive definite, pixels
+close to a splat's centre, NaN gradients."""
 import numpy as np
 import pytest
 
@@ -148,3 +149,36 @@ def test_second_pixel_close_to_the_centre(R, tile):
     got = grads["scales"].cpu().numpy().astype(np.float64)[:, 1]
     # some forty roundings of 6e-8 between the pixel and the scale
     np.testing.assert_allclose(got, ref, rtol=2e-5)
+
+
+@pytest.mark.parametrize("tile", [8, 16, 32])
+@pytest.mark.parametrize("output", ["alpha", "colour", "depth"])
+def test_nan_gradient_stays_with_its_pixel(R, tile, output):
+    # two splats of one wavefront that share no pixel: a NaN in an output's gradient at a pixel of the
+    # first leaves the shape, opacity and place of the second as they are without it
+    f, z = 100.0, 2.0
+    cam = scenes.Camera(tile, tile, f, f, tile / 2.0, tile / 2.0, I3, Z3)
+    px = np.array([[1.0, 3.0], [min(tile, 16) - 2.0, 4.0]])
+    means = np.concatenate([(px - tile / 2.0) * z / f, np.full((2, 1), z)], 1)
+    g = scenes.random_gaussians(np.random.default_rng(6), means, 0)
+    g.scales = np.full((2, 3), 0.5 * z / f, F32)
+    g.opacities = np.full(2, 0.7, F32)
+    _, images, saved = run_fwd(R, g, [cam], settings(tile=tile, lowpass=0.1))
+    d = saved.debug_export()
+    assert d["n_used"].max() == 1  # no pixel takes both
+    rng = np.random.default_rng(7)
+    out = [rng.standard_normal(k).astype(F32) for k in ((3, tile, tile), (tile, tile), (tile, tile))]
+    say("nan", tile, output)
+
+    def run():
+        c, e, a = (torch.from_numpy(v.copy()).cuda() for v in out)
+        return R.backward(saved, [c], [e], [a])
+
+    clean = run()
+    out[("colour", "depth", "alpha").index(output)][..., 3, 1] = np.nan
+    bad = run()
+    # (the sums of colour and depth gradients take the pixel's gradient times a weight of zero, and the
+    # depth's goes on into the means)
+    for k in ("scales", "quats", "opacities") + (("means",) if output != "depth" else ()):
+        assert torch.isnan(bad[k][0]).any(), k
+        assert torch.equal(bad[k][1], clean[k][1]), k  # (one sum a value: no order to differ in)
