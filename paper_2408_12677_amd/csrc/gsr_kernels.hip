@@ -650,27 +650,35 @@ __global__ __launch_bounds__(1024) void k_scan_u32(uint32_t* a, int count, unsig
 // The same scan of more than kSumMany pairs, in place, by tiles of kSumTile: their sums, then each
 // block adds up the sums in front of its tile and scans it.  One block over all 188k block sums
 // of sixteen views of 3M Gaussians took 336 us and over the 15k of eight views of 500k 32 us;
-// the two launches take 11 and 10.  With fewer the second launch costs what it saves.
+// the two launches take 11 and 10.  With fewer the second launch costs what it saves.  part: a
+// tile's pairs and records as 64-bit sums (its 65,536 records can cover 2^20 tiles each, and a
+// total past 2^32 has to show).
 constexpr int kSumTile = 256;
 constexpr int64_t kSumMany = 4096;
 
-__global__ __launch_bounds__(kSumTile) void k_sum_pairs(const uint2* a, int64_t count, uint2* part) {
+__global__ __launch_bounds__(kSumTile) void k_sum_pairs(const uint2* a, int64_t count, unsigned long long* part) {
   __shared__ uint32_t red[kSumTile / 64];
+  __shared__ unsigned long long red64[kSumTile / 64];
   const int64_t i = int64_t(blockIdx.x) * kSumTile + threadIdx.x;
   const uint2 v = i < count ? a[i] : make_uint2(0u, 0u);
-  const uint32_t x = block_sum_u32(v.x, red), y = block_sum_u32(v.y, red);
-  if (threadIdx.x == 0) part[blockIdx.x] = make_uint2(x, y);
+  unsigned long long x = v.x;
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+  if ((threadIdx.x & 63) == 0) red64[threadIdx.x >> 6] = x;
+  const uint32_t y = block_sum_u32(v.y, red);  // (its barrier also publishes red64)
+  if (threadIdx.x == 0) {
+    part[2 * blockIdx.x] = (red64[0] + red64[1]) + (red64[2] + red64[3]);
+    part[2 * blockIdx.x + 1] = y;
+  }
 }
 
-__global__ __launch_bounds__(kSumTile) void k_scan_pairs_down(uint2* a, int64_t count, const uint2* part,
+__global__ __launch_bounds__(kSumTile) void k_scan_pairs_down(uint2* a, int64_t count, const unsigned long long* part,
                                                               unsigned long long* totals, unsigned long long* host) {
   __shared__ unsigned long long red[kSumTile];
   const int t = threadIdx.x;
   unsigned long long bx = 0, by = 0;
   for (int i = t; i < int(blockIdx.x); i += kSumTile) {
-    const uint2 p = part[i];
-    bx += p.x;
-    by += p.y;
+    bx += part[2 * i];
+    by += part[2 * i + 1];
   }
   const int64_t i = int64_t(blockIdx.x) * kSumTile + t;
   const uint2 v = i < count ? a[i] : make_uint2(0u, 0u);
@@ -2796,14 +2804,17 @@ hipError_t launch_scan_small(uint32_t* a, int count, unsigned long long* total, 
   return hipGetLastError();
 }
 
-int64_t scan_pairs_words(int64_t count) { return count + (count > kSumMany ? (count + kSumTile - 1) / kSumTile : 0); }
+int64_t scan_pairs_words(int64_t count) {  // (two 64-bit sums, two of a's elements, a tile)
+  return count + (count > kSumMany ? 2 * ((count + kSumTile - 1) / kSumTile) : 0);
+}
 
 hipError_t launch_scan_pairs(uint2* blocksums, int64_t count, unsigned long long* totals, unsigned long long* host,
                              hipStream_t s) {
   if (count > kSumMany) {
     const int tiles = blocks_for(count, kSumTile);
-    k_sum_pairs<<<tiles, kSumTile, 0, s>>>(blocksums, count, blocksums + count);
-    k_scan_pairs_down<<<tiles, kSumTile, 0, s>>>(blocksums, count, blocksums + count, totals, host);
+    auto* part = reinterpret_cast<unsigned long long*>(blocksums + count);
+    k_sum_pairs<<<tiles, kSumTile, 0, s>>>(blocksums, count, part);
+    k_scan_pairs_down<<<tiles, kSumTile, 0, s>>>(blocksums, count, part, totals, host);
   } else {
     k_scan_pairs<<<1, 1024, 0, s>>>(blocksums, int(count), totals, host);
   }

@@ -70,6 +70,22 @@ def test_block_sums_of_many_gaussians(R, views, n):
             assert torch.equal(a[0], b[0])
 
 
+def test_more_pairs_than_keys_can_number(R):
+    # 1,048,577 splats over all 258 x 258 tiles: 7e10 pairs.  65,536 records of them alone have more
+    # than 2^32; the forward says so whether one block adds up the block sums or (as here) many do
+    n = 4096 * 256 + 1
+    params = [torch.zeros((n, 3)), torch.full((n, 3), 100.0), torch.zeros((n, 4)), torch.full((n,), 0.5),
+              torch.zeros((n, 1, 3))]
+    params[0][:, 2] = 2.0
+    params[2][:, 0] = 1.0
+    cam = scenes.Camera(2064, 2064, 1000.0, 1000.0, 1032.0, 1032.0, np.eye(3, dtype=np.float32),
+                        np.zeros(3, np.float32))
+    say("pairs")
+    for m in (n - 1, n):
+        with pytest.raises(Exception, match="2\\^32"):
+            R.forward(*[p[:m].cuda() for p in params], [cam], settings(tile=8))
+
+
 class _Pieces:
     """A caller's allocator that refuses blocks above `limit` bytes."""
 
