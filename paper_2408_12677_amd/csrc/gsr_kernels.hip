@@ -97,6 +97,14 @@ __device__ __forceinline__ uint32_t wave_add_scan(uint32_t v) {
   return v;
 }
 
+// Between LDS accesses of a wavefront's lanes that read what other lanes wrote: the hardware
+// carries out a wavefront's LDS accesses in order, and the fences keep the compiler's (no instruction).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ uint32_t block_sum_u32(uint32_t v, uint32_t* red) {
   v = wave_add_scan(v);
   const int nw = blockDim.x >> 6;
@@ -897,8 +905,9 @@ template <int ITEMS>
 __device__ __forceinline__ void wave_rank(const uint32_t (&key)[ITEMS], int shift, uint16_t* cnt,
                                           uint16_t (&rank)[ITEMS]) {
   const int lane = threadIdx.x & 63;
-  for (int i = lane; i < kSortDigits / 2; i += 64) reinterpret_cast<uint32_t*>(cnt)[i] = 0u;
-  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < kSortDigits / 64; ++i) cnt[64 * i + lane] = 0;
+  wave_lds_sync();
 #pragma unroll
   for (int r = 0; r < ITEMS; ++r) {
     const uint32_t d = (key[r] >> shift) & (kSortDigits - 1);
@@ -913,9 +922,9 @@ __device__ __forceinline__ void wave_rank(const uint32_t (&key)[ITEMS], int shif
     const uint32_t in = __builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0u));
     const uint32_t prior = cnt[d];
     rank[r] = uint16_t(prior + in);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
     if (in == 0) cnt[d] = uint16_t(prior + __popc(lo) + __popc(hi));
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_sync();
   }
 }
 
@@ -1209,7 +1218,7 @@ constexpr int kPlaceStage = 4096;   // pairs listed at once
 // The block's LDS, sized for the bins of a launch (place_lds bytes of dynamic LDS): a short one
 // lets more blocks share a CU.
 struct PlaceLds {
-  uint64_t* mask;   // [4][bins + 1] per wavefront and bin, the items that cover it
+  unsigned long long* mask;  // [4][bins + 1] per wavefront and bin, the items that cover it
   uint32_t* next;   // [bins] each bin's next free slot
   uint32_t* pre;    // [bins] the round's pairs in front of each bin
   uint32_t* woff;   // [bins] within a bin, the pairs of wavefronts 0, 0-1, 0-2 (8 bits each, from bit 8)
@@ -1222,7 +1231,7 @@ static size_t place_lds(int bins) { return size_t(bins + 1) * 32 + size_t(bins) 
 __device__ __forceinline__ PlaceLds place_carve(unsigned char* base, int bins) {
   PlaceLds L;
   L.bins = bins;
-  L.mask = reinterpret_cast<uint64_t*>(base);
+  L.mask = reinterpret_cast<unsigned long long*>(base);
   L.next = reinterpret_cast<uint32_t*>(base + size_t(bins + 1) * 32);
   L.pre = L.next + bins;
   L.woff = L.pre + bins;
@@ -1265,21 +1274,21 @@ template <class Emit>
 __device__ __forceinline__ void place_round(const PlaceLds& L, int nb, int lo, int hi, Emit&& emit) {
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   const int stride = L.bins + 1;
-  uint64_t* mask = L.mask + w * stride;
+  unsigned long long* mask = L.mask + w * stride;
   for (int x = lane; x <= nb; x += 64) mask[x] = 0ull;
-  __builtin_amdgcn_wave_barrier();
+  wave_lds_sync();
   if (lo <= hi) {
-    atomicXor(reinterpret_cast<unsigned long long*>(&mask[lo]), 1ull << lane);
-    atomicXor(reinterpret_cast<unsigned long long*>(&mask[hi + 1]), 1ull << lane);
+    atomicXor(&mask[lo], 1ull << lane);
+    atomicXor(&mask[hi + 1], 1ull << lane);
   }
-  __builtin_amdgcn_wave_barrier();
-  uint64_t carry = 0;
+  wave_lds_sync();
+  unsigned long long carry = 0;
   for (int x0 = 0; x0 < nb; x0 += 64) {
-    const uint64_t v = x0 + lane < nb ? mask[x0 + lane] : 0ull;
+    const unsigned long long v = x0 + lane < nb ? mask[x0 + lane] : 0ull;
     const uint32_t l = wave_xor_scan(uint32_t(v)), h = wave_xor_scan(uint32_t(v >> 32));
-    const uint64_t m = ((uint64_t(h) << 32) | l) ^ carry;
+    const unsigned long long m = ((static_cast<unsigned long long>(h) << 32) | l) ^ carry;
     if (x0 + lane < nb) mask[x0 + lane] = m;
-    carry ^= (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(h), 63))) << 32) |
+    carry ^= (static_cast<unsigned long long>(uint32_t(__builtin_amdgcn_readlane(int(h), 63))) << 32) |
              uint32_t(__builtin_amdgcn_readlane(int(l), 63));
   }
   __syncthreads();
@@ -1301,7 +1310,7 @@ __device__ __forceinline__ void place_round(const PlaceLds& L, int nb, int lo, i
   const uint32_t total = L.red[4];
   for (uint32_t p0 = 0; p0 < total; p0 += kPlaceStage) {
     for (int x = lane; x < nb; x += 64) {
-      const uint64_t m = mask[x];
+      const unsigned long long m = mask[x];
       uint32_t pos = L.pre[x] + (w == 0 ? 0u : (L.woff[x] >> (8 * w)) & 255u) - p0;  // (wraps in front of p0)
       const uint32_t code = (uint32_t(x) << 8) | uint32_t(64 * w);
       if (total <= uint32_t(kPlaceStage)) {
@@ -1437,13 +1446,15 @@ __global__ __launch_bounds__(kPlaceThreads) void k_bin_rows_place(ViewTable vt, 
                                                                   const unsigned long long* nvis, int64_t cap_vis,
                                                                   uint32_t* overflow, BinPlan plan) {
   extern __shared__ __align__(16) unsigned char s_dyn[];  // place_lds(bins) bytes, bins = min(rows, kPlaceBins)
-  __shared__ uint32_t s_rr[kRowRuns + 1][kPlaceThreads];  // the round's row runs, row k of item j at [k][j]
+  __shared__ union {
+    uint32_t rr[kRowRuns + 1][kPlaceThreads];   // the round's row runs, row k of item j at [k][j]
+    unsigned long long meta[kPlaceThreads];     // rows_meta's, before the rounds
+  } s;
   __shared__ uint32_t s_rid[kPlaceThreads], s_first[kPlaceThreads];
-  static_assert(sizeof(s_rr) >= kPlaceThreads * sizeof(unsigned long long), "s_rr serves rows_meta first");
   const int t = threadIdx.x, R = plan.rows;
   const PlaceLds L = place_carve(s_dyn, min(R, kPlaceBins));
   if (blockIdx.x == gridDim.x - 1)
-    rows_meta<kPlaceThreads>(vt, plan, overflow, reinterpret_cast<unsigned long long*>(&s_rr[0][0]));
+    rows_meta<kPlaceThreads>(vt, plan, overflow, s.meta);
   const int chunk = xcd_block(blockIdx.x, gridDim.x);
   const int64_t NV = clamp_count(nvis, cap_vis, overflow);
   const int64_t beg = int64_t(chunk) * kPlaceThreads * plan.rounds1;
@@ -1479,14 +1490,14 @@ __global__ __launch_bounds__(kPlaceThreads) void k_bin_rows_place(ViewTable vt, 
         uint32_t rr[kRowRuns];
         load_row_runs(rec, entry, lo <= hi, rr);
 #pragma unroll
-        for (int k = 0; k < kRowRuns; ++k) s_rr[k][t] = rr[k];
+        for (int k = 0; k < kRowRuns; ++k) s.rr[k][t] = rr[k];
       }
-      s_rr[kRowRuns][t] = rec.runs ? entry.y | kRunUncut : entry.y;
+      s.rr[kRowRuns][t] = rec.runs ? entry.y | kRunUncut : entry.y;
       s_rid[t] = entry.x;
       s_first[t] = first;
       place_round(L, nb, lo, hi, [&](uint32_t dst, int j, int bin) {
         const uint32_t k = rec.runs ? min(uint32_t(w0 + bin) - s_first[j], uint32_t(kRowRuns)) : uint32_t(kRowRuns);
-        if (int64_t(dst) < plan.cap_M) plan.rowlist[dst] = make_uint2(s_rid[j], s_rr[k][j]);
+        if (int64_t(dst) < plan.cap_M) plan.rowlist[dst] = make_uint2(s_rid[j], s.rr[k][j]);
       });
     }
   }
