@@ -200,10 +200,14 @@ class ArrayGroup {
       return GSR_OK;
     }
     ctx->err.clear();
+    const size_t had = list.size();
     for (const Item& it : items_) {
       void* q = nullptr;
       const gsr_status st = dev_alloc(ctx, ctx->stream, &q, it.bytes);
-      if (st != GSR_OK) return st;
+      if (st != GSR_OK) {  // (what was taken goes back, for a smaller request after this one)
+        for (; list.size() > had; list.pop_back()) dev_free(ctx, list.back(), ctx->stream);
+        return st;
+      }
       if (q) list.push_back(q);
       it.set(q);
     }
@@ -331,19 +335,29 @@ gsr_status make_saved(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_camera* ca
 gsr_status alloc_sort(gsr_saved* sv, int64_t cap_vis, int64_t cap_M, bool persistent) {
   sv->cap_vis = cap_vis;
   sv->cap_M = cap_M;
-  BinPlan& p = sv->plan;
-  p = bin_plan(sv->vt, cap_vis, cap_M);
-  const int64_t n1 = int64_t(p.rows) * p.nch1;
-  const int64_t nparts = (std::max(n1, p.cap_flat) + kScanTile - 1) / kScanTile;
-  ArrayGroup keep, work;
+  ArrayGroup keep;
   keep.add(&sv->vals, cap_M);
-  work.add(&sv->dk, cap_vis).add(&sv->dv, cap_vis).add(&sv->dk2, cap_vis).add(&sv->dv2, cap_vis);
-  work.add(&sv->hist, size_t(radix_hist_words(cap_vis, sv->V))).add(&sv->vstart, size_t(sv->V) + 1).add(&sv->dtot, 256);
-  work.add(&p.cnt1, size_t(n1)).add(&p.rowlist, cap_M).add(&p.rowinfo, size_t(p.rows));
-  work.add(&p.seg_start, size_t(p.rows) + 1).add(&p.cntF, size_t(p.cap_flat)).add(&p.part, size_t(nparts));
-  work.add(&p.ord, kOrderWords).add(&p.words, 4);
-  const gsr_status st = keep.take(sv->ctx, sv->blocks);
-  return st != GSR_OK ? st : work.take(sv->ctx, persistent ? sv->blocks : sv->temps);
+  gsr_status st = keep.take(sv->ctx, sv->blocks);
+  if (st != GSR_OK) return st;
+  BinPlan& p = sv->plan;
+  auto take_work = [&](int64_t max_tile_counts) {
+    p = bin_plan(sv->vt, cap_vis, cap_M, max_tile_counts);
+    const int64_t n1 = int64_t(p.rows) * p.nch1;
+    const int64_t nparts = (std::max(n1, p.cap_flat) + kScanTile - 1) / kScanTile;
+    ArrayGroup work;
+    work.add(&sv->dk, cap_vis).add(&sv->dv, cap_vis).add(&sv->dk2, cap_vis).add(&sv->dv2, cap_vis);
+    work.add(&sv->hist, size_t(radix_hist_words(cap_vis, sv->V))).add(&sv->vstart, size_t(sv->V) + 1).add(&sv->dtot, 256);
+    work.add(&p.cnt1, size_t(n1)).add(&p.rowlist, cap_M).add(&p.rowinfo, size_t(p.rows));
+    work.add(&p.seg_start, size_t(p.rows) + 1).add(&p.cntF, size_t(p.cap_flat)).add(&p.part, size_t(nparts));
+    work.add(&p.ord, kOrderWords).add(&p.words, 4);
+    return work.take(sv->ctx, persistent ? sv->blocks : sv->temps);
+  };
+  st = take_work(kMaxTileCounts);
+  if (st == GSR_ENOMEM && bin_plan(sv->vt, cap_vis, cap_M, kMinTileCounts).cap_flat < p.cap_flat) {
+    sv->ctx->err.clear();
+    st = take_work(kMinTileCounts);
+  }
+  return st;
 }
 
 TileQueue queue_of(const gsr_saved* sv) { return TileQueue{sv->order, sv->ctrl, sv->order_hint ? 1 : 0}; }

@@ -116,8 +116,10 @@ constexpr int64_t kMaxBinCounts = int64_t(1) << 22;  // entries of the binning's
 // entries of the (tile, segment) count array (soft).  It is sized by the pair capacity while the
 // row entries, some 5 to 15 times fewer, decide how many segments there are: with 2^22 a
 // 1752x1168 view of 70M pairs had 2,380 segments of 2,048 entries, hardly one for each block
-// that fits on the chip
+// that fits on the chip.  The array takes up to 64 MB beside the 12 bytes a pair of the
+// lists; where the memory is refused, up to 16 MB with the fewer, longer segments of kMinTileCounts
 constexpr int64_t kMaxTileCounts = int64_t(1) << 24;
+constexpr int64_t kMinTileCounts = int64_t(1) << 22;
 
 // One camera plus where its tiles and pixels live in the concatenated spaces.
 struct ViewDev {
@@ -316,7 +318,7 @@ hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
                              const unsigned long long* count, int64_t cap, const uint32_t* overflow, int key_bits,
                              bool* result_in_alt, int* passes, hipStream_t s, Timer* tm);
 // Sizes of a binning plan for capacities (cap_vis, cap_M); pointers are left null.
-BinPlan bin_plan(const ViewTable& vt, int64_t cap_vis, int64_t cap_M);
+BinPlan bin_plan(const ViewTable& vt, int64_t cap_vis, int64_t cap_M, int64_t max_tile_counts);
 // exact_k > 0: per tile row only the columns the ellipse d^T Q d <= exact_k^2 reaches.
 // Uses the control words' overflow word.  Also writes the tile queue's order by
 // decreasing expected work: hint[t] (a previous forward's longest contributor count of

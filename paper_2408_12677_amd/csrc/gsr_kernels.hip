@@ -2903,7 +2903,7 @@ hipError_t launch_radix_sort(uint32_t* keys, uint32_t* vals, uint32_t* keys_alt,
   return hipGetLastError();
 }
 
-BinPlan bin_plan(const ViewTable& vt, int64_t cap_vis, int64_t cap_M) {
+BinPlan bin_plan(const ViewTable& vt, int64_t cap_vis, int64_t cap_M, int64_t max_tile_counts) {
   // one round of 256 items per block while the count arrays stay within kMaxBinCounts
   // entries; more rounds (fewer, longer chunks and segments) beyond that
   constexpr int64_t PT = kPlaceThreads;
@@ -2912,7 +2912,7 @@ BinPlan bin_plan(const ViewTable& vt, int64_t cap_vis, int64_t cap_M) {
   const int64_t max_chunks = std::max<int64_t>(1, kMaxBinCounts / std::max(1, p.rows));
   p.rounds1 = int(std::max<int64_t>(1, (cap_vis + PT * max_chunks - 1) / (PT * max_chunks)));
   p.nch1 = int(std::max<int64_t>(1, (cap_vis + PT * p.rounds1 - 1) / (PT * p.rounds1)));
-  const int64_t max_segs = std::max<int64_t>(1024, kMaxTileCounts / std::max(1, vt.max_tiles_x));
+  const int64_t max_segs = std::max<int64_t>(1024, max_tile_counts / std::max(1, vt.max_tiles_x));
   p.rounds2 = int(std::max<int64_t>(1, (cap_M + PT * max_segs - 1) / (PT * max_segs)));
   const int64_t S2 = PT * int64_t(p.rounds2);
   const int64_t segs = (cap_M + S2 - 1) / S2;

@@ -135,6 +135,54 @@ def test_allocator_that_refuses_one_large_block(R, limit, separate):
     saved2.free()
 
 
+class _Budget(_Pieces):
+    """A caller's allocator that holds at most `limit` bytes at a time."""
+
+    def __init__(self, limit):
+        super().__init__(limit)
+        self.now, self.peak, self.size = 0, 0, {}
+
+    def alloc(self, nbytes, stream):
+        if self.now + nbytes > self.limit:
+            return 0
+        p = _Pieces.alloc(self, nbytes, stream)
+        self.size[p] = nbytes
+        self.now += nbytes
+        self.peak = max(self.peak, self.now)
+        return p
+
+    def free(self, ptr, stream):
+        _Pieces.free(self, ptr, stream)
+        self.now -= self.size.pop(ptr)
+
+
+def test_allocator_without_room_for_the_larger_plan(R):
+    # 10.3M pairs over 256 columns: 10.3M tile counts (41 MB), of which a third do where the memory for
+    # all is refused: the same images and keys
+    base = scenes.make_cfg1().gaussians
+    g = base.subset(np.arange(0, base.n, 2))
+    g.scales = (g.scales * 60).astype(np.float32)
+    f = 2048.0
+    cam = scenes.Camera(2048, 512, f, f, 1024.0, 256.0, np.eye(3, dtype=np.float32), np.zeros(3, np.float32))
+    params, s = to_dev(g), settings(tile=8)
+    results, peak = [], 1 << 40
+    for spare in (0, 8 << 20):
+        budget = _Budget(peak - spare)
+        ctx = R.Context(torch.cuda.current_device(), torch.cuda.current_stream().cuda_stream, budget)
+        say("budget", budget.limit)
+        with R.using(ctx):
+            images, saved = R.forward(*params, [cam], s)
+            info, dbg = saved.info(), saved.debug_export()
+            saved.free()
+        peak = budget.peak
+        results.append((images[0], dbg))
+    assert 9 << 20 < info["num_keys"] < 12 << 20
+    for a, b in zip(results[0][0], results[1][0]):
+        assert torch.equal(a, b)
+    for k in ("keys", "values", "ranges"):
+        np.testing.assert_array_equal(results[0][1][k], results[1][1][k])
+
+
 @pytest.mark.parametrize("views,n", [(1, 2), (1, 4096), (5, 4096), (1, 4097), (2, 16384), (1, 16385), (3, 20000),
                                      (1, 458752), (2, 458753), (1, 917504), (2, 917505)])
 def test_depth_sort_sizes(R, views, n):
