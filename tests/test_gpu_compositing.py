@@ -54,3 +54,28 @@ def test_backward_work_items_over_many_tiles(R, w, h):
             scale = float(first[k].abs().max())
             # float sums of the same terms in another order: 1e-5 of the group's largest value
             assert float((first[k] - other[k]).abs().max()) <= 1e-5 * scale + 1e-20, (k, scale)
+
+
+@pytest.mark.parametrize("w,h", [(512, 512), (520, 512), (1024, 600)])
+def test_work_items_of_small_tiles_cover_every_entry(R, w, h):
+    # the gradients over 4,096, 4,160 and 9,600 tiles of 8 (beyond 4,096 the items are placed by sums of
+    # slices) equal those over a quarter of the tiles of 16, where every block counts for itself: the
+    # same pixels take the same splats, summed in another order
+    g = scenes.make_cfg1().gaussians
+    f = float(max(w, h))
+    cam = scenes.Camera(w, h, f, f, w / 2.0, h / 2.0, np.eye(3, dtype=np.float32), np.zeros(3, np.float32))
+    gc = torch.from_numpy(np.random.default_rng(w + h).standard_normal((3, h, w)).astype(np.float32)).cuda()
+    params = to_dev(g)
+    say("items of 8 and 16", w, h)
+    grads, images = [], []
+    for tile in (8, 16):
+        im, saved = R.forward(*params, [cam], settings(tile=tile))
+        images.append(im[0])
+        grads.append(R.backward(saved, [gc]))
+    for a, b in zip(*images):
+        assert torch.equal(a, b)
+    for k in grads[0]:
+        # sums of up to 10^5 terms of either sign in another order, through the projection's chain rule: 1e-4
+        # of the group's largest value (an item left out or taken twice changes whole splats)
+        scale = float(grads[0][k].abs().max())
+        assert float((grads[0][k] - grads[1][k]).abs().max()) <= 1e-4 * scale, k
