@@ -24,7 +24,12 @@ def hipcc() -> str:
     raise RuntimeError("hipcc not found")
 
 
-def command(out: str = LIB) -> list:
+# matrix-core results in ordinary registers (no moves to and from accumulation registers): an option
+# of the compiler's own, which another release may not have
+MFMA_FORM = ("-mllvm", "-amdgpu-mfma-vgpr-form=1")
+
+
+def command(out: str = LIB, extra: tuple = MFMA_FORM) -> list:
     return [
         hipcc(), f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-shared",
         "-I", os.path.join(ROOT, "include"),
@@ -34,9 +39,7 @@ def command(out: str = LIB) -> list:
         "-munsafe-fp-atomics",
         # no packed-FP32 (v_pk_*_f32) instruction selection
         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        # matrix-core results in ordinary registers (no moves to and from accumulation registers)
-        "-mllvm", "-amdgpu-mfma-vgpr-form=1",
-        "-Wall", "-Wno-unused-function",
+        *extra, "-Wall", "-Wno-unused-function",
         "-o", out, *SOURCES,
     ]
 
@@ -52,6 +55,8 @@ def build(force: bool = True, verbose: bool = False) -> str:
     if verbose:
         print(" ".join(cmd), file=sys.stderr)
     res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0 and "amdgpu-mfma-vgpr-form" in res.stderr:  # the option is not known: the same results without
+        res = subprocess.run(command(tmp, ()), capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stdout + res.stderr)
     os.replace(tmp, LIB)
