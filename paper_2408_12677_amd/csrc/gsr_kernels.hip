@@ -370,18 +370,7 @@ __device__ __forceinline__ float splat_alpha(float dx, float dy, float ap, float
   return o * G;
 }
 
-// LDS copy of record id for the compositing kernels: r0 = (mu_x, mu_y, a', b'),
-// r1 = (c', opacity, depth, 2 a'), rgb = (r, g, b, 2 c') with (a', b', c') as above.
-__device__ __forceinline__ void stage_record(const Records& rec, uint32_t id, float4& r0, float4& r1, float4& rgb) {
-  const float4 g0 = rec.r0[id], g1 = rec.r1[id];
-  const float ap = kNegHalfLog2e * g0.z, cp = kNegHalfLog2e * g1.x;
-  r0 = make_float4(g0.x, g0.y, ap, (2.f * kNegHalfLog2e) * g0.w);
-  r1 = make_float4(cp, g1.y, g1.z, ap + ap);
-  const float4 c = rec.rgb[id];
-  rgb = make_float4(c.x, c.y, c.z, cp + cp);
-}
-
-// The same split as the matrix-core kernels read it: the centre, (a', b', c', opacity) and
+// Record id as the compositing kernels stage it: the centre, (a', b', c', opacity) as above and
 // (colour, depth).
 __device__ __forceinline__ void stage_record(const Records& rec, uint32_t id, float& mx, float& my, float4& sq,
                                              float4& col) {
@@ -1972,10 +1961,10 @@ __global__ __launch_bounds__(256) void k_count_used(ViewTable vt, Rules ru, Reco
   const float fpx = float(px), fpy = float(py);
   uint32_t used = 0;
   for (uint32_t j = 0; j < nc && rg.x + j < rg.y; ++j) {
-    float4 r0, r1, rgb;
-    stage_record(rec, vals[rg.x + j], r0, r1, rgb);
-    float G;
-    const float a = splat_alpha(fpx - r0.x, fpy - r0.y, r0.z, r0.w, r1.x, r1.y, G);
+    float mx, my, G;
+    float4 sq, col;
+    stage_record(rec, vals[rg.x + j], mx, my, sq, col);
+    const float a = splat_alpha(fpx - mx, fpy - my, sq.x, sq.y, sq.z, sq.w, G);
     used += !(a < ru.amin) ? 1u : 0u;
   }
   n_used[i] = used;
