@@ -786,8 +786,9 @@ __global__ __launch_bounds__(kProjThreads) void k_compact(int64_t n, Records rec
 // a store per key, before).  Views of up to kSmallMost keys are sorted by one block each, in LDS,
 // all passes in one launch.
 // Kernel trace of a whole sort, before -> after: 1.9k keys 43 -> 13 us, 12k 49 -> 41, 85k 51 -> 39,
-// 335k 73 -> 51 (captured), 1M 103 -> 70, 2.7M in eight views 231 -> 126.  The small ones are chains of latencies (2 us of each launch), the large ones VALU
-// issue of the ranking (half) and the scattered writes.
+// 335k 73 -> 51 (captured), 1M 103 -> 70, 2.7M in eight views 231 -> 126.  The small ones are
+// chains of latencies (2 us of each launch), the large ones VALU issue of the ranking (half) and
+// the scattered writes.
 // ------------------------------------------------------------------------------------
 // 8-bit digits: wider ones (11 bits, three passes for a depth key) ran slower on MI355X,
 // their histograms being written and read across many more cache lines
@@ -1980,8 +1981,8 @@ __global__ __launch_bounds__(256) void k_count_used(ViewTable vt, Rules ru, Reco
 // block that reserved its places with an atomic instead got them in random order, and without
 // the longest-first order the backward over eight 876x584 views took 955 to 1213 us, with it 921).
 // One block for all 128k tiles of sixteen 1752x1168 views made the captured loss take 1252 us,
-// now 308 and 5 for the sums (eight views of 876x584: 147 -> 54 and 5, one of 640x480: 12 -> 9.6); one reservation per
-// tile by the forward slowed that by a fifth over eight views.
+// now 308 and 5 for the sums (eight views of 876x584: 147 -> 54 and 5, one of 640x480: 12 -> 9.6); one
+// reservation per tile by the forward slowed that by a fifth over eight views.
 constexpr int kListExact = 4096;
 
 __device__ __forceinline__ uint32_t tile_items(const uint32_t* order, int i, int stride, const Ckpt& ck, uint32_t& t) {
@@ -2027,8 +2028,8 @@ __global__ __launch_bounds__(256) void k_bwd_items(const uint32_t* order, int to
 // K7: L1 loss and its gradient with respect to the rendered colour and depth
 // ------------------------------------------------------------------------------------
 // host_flag (a captured step's, else null): the host's pinned copy of the sticky overflow word, which
-// nothing after the forward raises.  With order non-null (a captured step) the first blocks also list the backward's work
-// items (list_bwd_items) for the tiles the forward just composited.
+// nothing after the forward raises.  With order non-null (a captured step) the first blocks also list the
+// backward's work items (list_bwd_items) for the tiles the forward just composited.
 __global__ __launch_bounds__(256) void k_loss_l1(ViewTable vt, float depth_w, float* partial, const uint32_t* order,
                                                 int total_tiles, int stride, Ckpt ck, uint32_t* ctrl, uint32_t* host_flag) {
   __shared__ float red[4];
@@ -2294,10 +2295,9 @@ __device__ __forceinline__ void flush_splat_sums(float (&s_g)[NW][SB][16], const
 }
 
 template <int TS, int PPL>
-__global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS == 32 ? 4 : 5))) void k_blend_bwd2(ViewTable vt, Rules ru, Records rec,
-                                                            const uint2* ranges, const uint32_t* vals,
-                                                            const float* T_final, const uint32_t* n_contrib,
-                                                            float* grad2d, TileQueue q, Ckpt ck) {
+__global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS == 32 ? 4 : 5))) void k_blend_bwd2(
+    ViewTable vt, Rules ru, Records rec, const uint2* ranges, const uint32_t* vals, const float* T_final,
+    const uint32_t* n_contrib, float* grad2d, TileQueue q, Ckpt ck) {
   constexpr int NT = TS * TS / PPL;  // threads
   constexpr int NW = NT / 64;        // wavefronts
   constexpr int WX = TS < 16 ? TS : 16;  // a wavefront's pixels: WX wide, 8 high (splat_sums needs
@@ -2365,8 +2365,9 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
       __syncthreads();
       // Groups of staged entries, back to front.  First everything that does not depend on the
       // running T and B, for the whole group at once (its LDS reads and exponentials overlap);
-      // g . (colour, depth) as rank-1 updates on the matrix cores (four entries each).  Then the recurrences and sums, entry by entry;
-      // entries that no pixel of the wavefront takes are left out.  A lane that does not take
+      // g . (colour, depth) as rank-1 updates on the matrix cores (four entries each).  Then the
+      // recurrences and sums, entry by entry; entries that no pixel of the wavefront takes are
+      // left out.  A lane that does not take
       // an entry (past its list or the stage, or below the skip threshold) has alpha = 0, which
       // leaves T and B unchanged (1 / (1 - 0) = 1 exactly) and gives u = w = 0.
       //
@@ -2374,10 +2375,11 @@ __global__ __launch_bounds__(TS* TS / PPL) __attribute__((amdgpu_waves_per_eu(TS
       // latency where few are; measured issue costs per wavefront instruction are 2 cycles for
       // adds, multiplies and fmas, 4 for compares, selects, min and DPP, 8 for exponentials,
       // reciprocals, lane swaps and the 4x4x1 products.  Against one entry at a time and centre
-      // atomics of their own: 15.7 -> 12.9 ms over sixteen
-      // 1752x1168 views, 1105 -> 925 us over eight uneven ones, 175 -> 124 us and 149 -> 122 us on
-      // one 876x584 (170k splats) and one 640x480 view (500k).  Taking the sums as matrix products
-      // (16x16x4, splats by pixels) was slower over many views (19.4 ms): they share the
+      // atomics of their own: 15.1 -> 12.7 ms over sixteen 1752x1168 views, 1228 -> 979 us over
+      // eight uneven ones, 204 -> 145 us and 163 -> 137 us on one 876x584 (170k splats) and one
+      // 640x480 view (500k).  The clamp tested at every pixel, the moments from each pixel's own
+      // offset and the select of u cost 2.2% of it over many views.  Taking the sums as matrix products
+      // (16x16x4, splats by pixels) was slower over many views (by a half): they share the
       // VALU's issue at 32 cycles each and need 30 KB of LDS a block.
       uint64_t hit = 0;  // staged splats some pixel of the wavefront takes (wavefront-uniform)
       for (int jb = (min(nstage, wmax - bstart) - 1) & ~(GS - 1); jb >= 0; jb -= GS) {
@@ -2943,7 +2945,8 @@ hipError_t launch_bin(const ViewTable& vt, int64_t n, const Records& rec, const 
   scan_u32(plan.cnt1, n1, nullptr, plan.part, plan.words, s);
   E(K_BIN_SCAN);
   B(K_BIN_SCATTER);
-  k_bin_rows_place<<<xcd_grid(plan.nch1), kPlaceThreads, place_lds(std::min(plan.rows, kPlaceBins)), s>>>(vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
+  k_bin_rows_place<<<xcd_grid(plan.nch1), kPlaceThreads, place_lds(std::min(plan.rows, kPlaceBins)), s>>>(
+      vt, n, rec, dvals, nvis, cap_vis, overflow, plan);
   E(K_BIN_SCATTER);
   B(K_BIN_COUNT);
   k_bin_tiles_count<<<g_segs, 256, (size_t(vt.max_tiles_x) + 1) * 4, s>>>(vt, plan, rec, exact_k, tile, hint);
@@ -2952,7 +2955,8 @@ hipError_t launch_bin(const ViewTable& vt, int64_t n, const Records& rec, const 
   scan_u32(plan.cntF, plan.cap_flat, plan.words + 2, plan.part, plan.words + 3, s);
   E(K_BIN_SCAN);
   B(K_BIN_SCATTER);
-  k_bin_tiles_place<<<g_segs, kPlaceThreads, place_lds(std::min(vt.max_tiles_x, kPlaceBins)), s>>>(vt, plan, vals, overflow, ranges, hint, order);
+  k_bin_tiles_place<<<g_segs, kPlaceThreads, place_lds(std::min(vt.max_tiles_x, kPlaceBins)), s>>>(
+      vt, plan, vals, overflow, ranges, hint, order);
   E(K_BIN_SCATTER);
   if (!hint) {  // the order not taken by the placement above
     B(K_TILE_ORDER);
