@@ -349,7 +349,7 @@ gsr_status alloc_sort(gsr_saved* sv, int64_t cap_vis, int64_t cap_M, bool persis
     work.add(&sv->hist, size_t(radix_hist_words(cap_vis, sv->V))).add(&sv->vstart, size_t(sv->V) + 1).add(&sv->dtot, 256);
     work.add(&p.cnt1, size_t(n1)).add(&p.rowlist, cap_M).add(&p.rowinfo, size_t(p.rows));
     work.add(&p.seg_start, size_t(p.rows) + 1).add(&p.cntF, size_t(p.cap_flat)).add(&p.part, size_t(nparts));
-    work.add(&p.ord, kOrderWords).add(&p.words, 4);
+    work.add(&p.ord, kOrderWords).add(&p.okey, size_t(sv->vt.total_tiles)).add(&p.words, 4);
     return work.take(sv->ctx, persistent ? sv->blocks : sv->temps);
   };
   st = take_work(kMaxTileCounts);

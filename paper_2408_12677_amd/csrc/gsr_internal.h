@@ -231,6 +231,7 @@ struct BinPlan {
   uint32_t* cntF;        // flat (tile, segment) counts, then exclusive offsets
   uint32_t* part;        // partial sums of the device-wide scans
   uint32_t* ord;         // [kOrderWords] bucket counters and cursors of the tile order, zero at a step's start
+  uint16_t* okey;        // [tiles] the tiles' buckets, as the counts took them from the work hint
   unsigned long long* words;  // [0] row entries, [1] segments, [2] flat size, [3] pairs placed
 };
 

@@ -1545,18 +1545,16 @@ __device__ __forceinline__ uint32_t work_bucket(uint32_t w) {
   return 1u + 8u * e + m;
 }
 
-// The queue order of `total` tiles by one whole block of NT threads (LDS: cnt and start
-// of kOrderBuckets words, red of NT / 64): bucket counts, their scan heaviest bucket first,
-// then each tile's slot (the order inside a bucket is arbitrary).  Key: the hint, or
-// without one the list length.
+// The queue order of `total` tiles by their list lengths, by one whole block of NT threads (LDS:
+// cnt and start of kOrderBuckets words, red of NT / 64): bucket counts, their scan heaviest
+// bucket first, then each tile's slot (the order inside a bucket is arbitrary).
 template <int NT>
-__device__ void tile_order_block(const uint2* ranges, const uint32_t* hint, int total, uint32_t* order,
-                                 uint32_t* cnt, uint32_t* start, uint32_t* red) {
+__device__ void tile_order_block(const uint2* ranges, int total, uint32_t* order, uint32_t* cnt, uint32_t* start,
+                                 uint32_t* red) {
   const int t = threadIdx.x;
   for (int b = t; b < kOrderBuckets; b += NT) cnt[b] = 0;
   __syncthreads();
   auto key = [&](int i) {
-    if (hint) return work_bucket(hint[i]);
     const uint2 r = ranges[i];
     return work_bucket(r.y - r.x);
   };
@@ -1587,25 +1585,31 @@ __device__ void tile_order_block(const uint2* ranges, const uint32_t* hint, int 
 // (tile_order_count), the placement's blocks then know where every bucket starts and take
 // places in it (tile_order_place).  ord: kOrderBuckets counters and as many cursors, zero at the
 // start of the step.  (By one block, the order of 128k tiles took longer than the placement.)
-__device__ void tile_order_count(const uint32_t* hint, int total, uint32_t* ord, uint32_t* cnt) {
+// The hint is read once, its buckets kept in okey: another forward of the context, on a stream that
+// the caller changed to, may be writing it, and places taken by other buckets than were counted
+// would leave the queue with tiles missing and run past its end.
+__device__ void tile_order_count(const uint32_t* hint, int total, uint32_t* ord, uint16_t* okey, uint32_t* cnt) {
   if (int(blockIdx.x) * 256 >= total) return;  // block-uniform
   for (int b = threadIdx.x; b < kOrderBuckets; b += 256) cnt[b] = 0;
   __syncthreads();
-  for (int i = int(blockIdx.x) * 256 + int(threadIdx.x); i < total; i += int(gridDim.x) * 256)
-    atomicAdd(&cnt[work_bucket(hint[i])], 1u);
+  for (int i = int(blockIdx.x) * 256 + int(threadIdx.x); i < total; i += int(gridDim.x) * 256) {
+    const uint32_t b = work_bucket(hint[i]);
+    okey[i] = uint16_t(b);
+    atomicAdd(&cnt[b], 1u);
+  }
   __syncthreads();
   for (int b = threadIdx.x; b < kOrderBuckets; b += 256)
     if (cnt[b]) atomicAdd(&ord[b], cnt[b]);
 }
 
-__device__ void tile_order_place(const uint32_t* hint, int total, uint32_t* ord, uint32_t* order, uint32_t* cnt,
+__device__ void tile_order_place(const uint16_t* okey, int total, uint32_t* ord, uint32_t* order, uint32_t* cnt,
                                  uint32_t* start, uint32_t* red) {
   if (int(blockIdx.x) * 256 >= total) return;  // block-uniform
   const int t = threadIdx.x;
   for (int b = t; b < kOrderBuckets; b += 256) cnt[b] = 0;
   __syncthreads();
   // this block's tiles of each bucket (their rank in it is kept in the loop below, so count first)
-  for (int i = int(blockIdx.x) * 256 + t; i < total; i += int(gridDim.x) * 256) atomicAdd(&cnt[work_bucket(hint[i])], 1u);
+  for (int i = int(blockIdx.x) * 256 + t; i < total; i += int(gridDim.x) * 256) atomicAdd(&cnt[okey[i]], 1u);
   // heaviest bucket first: position t of the descending order is bucket kOrderBuckets - 1 - t; bucket 0,
   // the last, starts after all others
   const uint32_t c = ord[kOrderBuckets - 1 - t];
@@ -1618,15 +1622,14 @@ __device__ void tile_order_place(const uint32_t* hint, int total, uint32_t* ord,
   static_assert(kOrderBuckets == 257, "one bucket per thread and bucket 0");
   __syncthreads();
   for (int i = int(blockIdx.x) * 256 + t; i < total; i += int(gridDim.x) * 256)
-    order[atomicAdd(&start[work_bucket(hint[i])], 1u)] = uint32_t(i);
+    order[atomicAdd(&start[okey[i]], 1u)] = uint32_t(i);
   __syncthreads();
 }
 
-__global__ __launch_bounds__(1024) void k_tile_order(const uint2* ranges, const uint32_t* hint, int total,
-                                                    uint32_t* order) {
+__global__ __launch_bounds__(1024) void k_tile_order(const uint2* ranges, int total, uint32_t* order) {
   __shared__ uint32_t cnt[kOrderBuckets], start[kOrderBuckets];
   __shared__ uint32_t red[16];
-  tile_order_block<1024>(ranges, hint, total, order, cnt, start, red);
+  tile_order_block<1024>(ranges, total, order, cnt, start, red);
 }
 
 // stage 2 counts: tile-column histogram of one segment of a row list, one block per segment
@@ -1642,7 +1645,7 @@ __global__ __launch_bounds__(256) void k_bin_tiles_count(ViewTable vt, BinPlan p
   extern __shared__ uint32_t hist[];  // max_tiles_x + 1 words
   __shared__ uint32_t s_cnt[kOrderBuckets], s_red[4], s_carry;
   const int t = threadIdx.x;
-  if (hint) tile_order_count(hint, vt.total_tiles, plan.ord, s_cnt);
+  if (hint) tile_order_count(hint, vt.total_tiles, plan.ord, plan.okey, s_cnt);
   const unsigned long long S = plan.words[1];
   for (uint32_t s = blockIdx.x; s < S; s += gridDim.x) {
     const Segment g = segment_of(vt, plan, s);
@@ -1711,15 +1714,15 @@ __device__ __forceinline__ uint2 tile_range(const ViewTable& vt, const BinPlan& 
 // queue's order
 __global__ __launch_bounds__(kPlaceThreads) void k_bin_tiles_place(ViewTable vt, BinPlan plan, uint32_t* vals,
                                                                    const uint32_t* overflow, uint2* ranges,
-                                                                   const uint32_t* hint, uint32_t* order) {
+                                                                   int hinted, uint32_t* order) {
   extern __shared__ __align__(16) unsigned char s_dyn[];  // place_lds(bins) bytes, bins = min(max_tiles_x, kPlaceBins)
   __shared__ uint32_t s_rid[kPlaceThreads];
   const int t = threadIdx.x;
   const PlaceLds L = place_carve(s_dyn, min(vt.max_tiles_x, kPlaceBins));
-  if (hint) {  // (in the stage's LDS, before the placement uses it)
+  if (hinted) {  // (in the stage's LDS, before the placement uses it)
     uint32_t* cnt = reinterpret_cast<uint32_t*>(L.stage);
     static_assert(kPlaceStage * 2 >= 2 * kOrderBuckets * 4, "the stage holds the counters and starts");
-    tile_order_place(hint, vt.total_tiles, plan.ord, order, cnt, cnt + kOrderBuckets, L.red);
+    tile_order_place(plan.okey, vt.total_tiles, plan.ord, order, cnt, cnt + kOrderBuckets, L.red);
   }
   for (int i = int(blockIdx.x) * kPlaceThreads + t; i < vt.total_tiles; i += int(gridDim.x) * kPlaceThreads)
     ranges[i] = tile_range(vt, plan, overflow, i);
@@ -2929,7 +2932,7 @@ hipError_t launch_bin(const ViewTable& vt, int64_t n, const Records& rec, const 
   if (cap_vis == 0 || plan.cap_M == 0 || plan.rows == 0) {
     k_fill_u32<<<blocks_for(int64_t(vt.total_tiles) * 2, 256), 256, 0, s>>>(reinterpret_cast<uint32_t*>(ranges), 0u,
                                                                              int64_t(vt.total_tiles) * 2);
-    k_tile_order<<<1, 1024, 0, s>>>(ranges, hint, vt.total_tiles, order);
+    k_tile_order<<<1, 1024, 0, s>>>(ranges, vt.total_tiles, order);
     return hipGetLastError();
   }
   auto B = [&](int k) { if (tm) tm->begin(k); };
@@ -2956,11 +2959,11 @@ hipError_t launch_bin(const ViewTable& vt, int64_t n, const Records& rec, const 
   E(K_BIN_SCAN);
   B(K_BIN_SCATTER);
   k_bin_tiles_place<<<g_segs, kPlaceThreads, place_lds(std::min(vt.max_tiles_x, kPlaceBins)), s>>>(
-      vt, plan, vals, overflow, ranges, hint, order);
+      vt, plan, vals, overflow, ranges, hint ? 1 : 0, order);
   E(K_BIN_SCATTER);
   if (!hint) {  // the order not taken by the placement above
     B(K_TILE_ORDER);
-    k_tile_order<<<1, 1024, 0, s>>>(ranges, hint, vt.total_tiles, order);
+    k_tile_order<<<1, 1024, 0, s>>>(ranges, vt.total_tiles, order);
     E(K_TILE_ORDER);
   }
   return hipGetLastError();

@@ -183,6 +183,34 @@ def test_allocator_without_room_for_the_larger_plan(R):
         np.testing.assert_array_equal(results[0][1][k], results[1][1][k])
 
 
+def test_work_hint_while_another_stream_writes_it(R):
+    # a context whose stream is changed without waiting: the second forward reads the work hint of the
+    # tile grid while the first one's compositing, on the other stream, writes it.  Whatever order of
+    # the tiles comes of it, every tile is composited once
+    g = scenes.make_cfg2(n=60000).gaussians
+    base = scenes.make_cfg2(n=16).cameras[0]
+    s = settings(tile=8)
+    params = to_dev(g)
+    cams = [scenes.Camera(640, 480, f, f, 320.0, 240.0, base.R, base.t) for f in (150.0, 600.0)]
+    wanted = [R.forward(*params, [c], s)[0][0] for c in cams]
+    streams = [torch.cuda.Stream() for _ in cams]
+    ctx = R.Context(torch.cuda.current_device(), streams[0].cuda_stream)
+    torch.cuda.synchronize()
+    say("two streams")
+    for _ in range(10):
+        kept = []
+        with R.using(ctx):
+            for k in (0, 1):
+                ctx.lib.gsr_ctx_set_stream(ctx.h, streams[k].cuda_stream)
+                kept.append(R.forward(*params, [cams[k]], s))
+        torch.cuda.synchronize()
+        for (images, saved), want in zip(kept, wanted):
+            for a, b in zip(images[0], want):
+                assert torch.equal(a, b)
+            saved.free()
+        torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("views,n", [(1, 2), (1, 4096), (5, 4096), (1, 4097), (2, 16384), (1, 16385), (3, 20000),
                                      (1, 458752), (2, 458753), (1, 917504), (2, 917505)])
 def test_depth_sort_sizes(R, views, n):
