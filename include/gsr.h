@@ -219,7 +219,9 @@ typedef struct gsr_alloc {
 
 /* Create a context on HIP device `device` enqueuing on `hip_stream` (a hipStream_t;
  * NULL = the null stream).  alloc (copied; may be NULL): the caller's allocator for the
- * library's device memory; NULL takes it from the device's stream-ordered memory pool.
+ * library's device memory; NULL takes it from the device's stream-ordered memory pool, and
+ * the context keeps blocks that its calls have given back for its next ones (at most a 64th of the
+ * device's memory) until gsr_ctx_set_stream names another stream or gsr_ctx_destroy.
  * EDEVICE when the device cannot be used; EINVAL for an allocator without both functions. */
 gsr_status gsr_ctx_create(int32_t device, void* hip_stream, const gsr_alloc* alloc, gsr_ctx** out);
 gsr_status gsr_ctx_destroy(gsr_ctx* ctx);

@@ -1,5 +1,7 @@
 """GPU binning against the oracle's sorted keys: more tile columns and rows than one window of
 bins, more pairs in a round than one listing holds, chunks that span several small views."""
+import threading
+
 import numpy as np
 import pytest
 
@@ -181,6 +183,46 @@ def test_allocator_without_room_for_the_larger_plan(R):
         assert torch.equal(a, b)
     for k in ("keys", "values", "ranges"):
         np.testing.assert_array_equal(results[0][1][k], results[1][1][k])
+
+
+def test_states_taken_and_given_back_in_any_order(R):
+    # forwards of changing sizes on one context, their states freed in another order (some by a second
+    # thread, some by their owners going away), blocks going round between them: every state that is
+    # alive keeps its own memory
+    base = scenes.make_cfg1()
+    rng = np.random.default_rng(11)
+    ctx = R.Context(torch.cuda.current_device(), torch.cuda.current_stream().cuda_stream)
+    cases = []
+    for n in (40, 400, 900, 1500, 2000):
+        g = base.gaussians.subset(np.arange(n))
+        cam = base.cameras[0].crop(0, 0, 48 + n // 25, 40 + n // 40)
+        params = to_dev(g)
+        images, saved = R.forward(*params, [cam], settings(tile=16))
+        gc = torch.from_numpy(rng.standard_normal(images[0][0].shape).astype(np.float32)).cuda()
+        cases.append((params, cam, gc, images[0][0].clone(), R.backward(saved, [gc])))
+    say("states")
+    alive = []
+    with R.using(ctx):
+        for _ in range(120):
+            if len(alive) < 6 and rng.random() < 0.6:
+                c = cases[rng.integers(len(cases))]
+                images, saved = R.forward(*c[0], [c[1]], settings(tile=16))
+                assert torch.equal(images[0][0], c[3])
+                alive.append((c, saved))
+            elif alive:
+                (params, cam, gc, image, want), saved = alive.pop(rng.integers(len(alive)))
+                grads = R.backward(saved, [gc])
+                for k in want:  # (the same terms, summed in another order)
+                    assert float((grads[k] - want[k]).abs().max()) <= 1e-5 * float(want[k].abs().max()) + 1e-20, k
+                how = rng.integers(3)
+                if how == 0:
+                    saved.free()
+                elif how == 1:
+                    th = threading.Thread(target=saved.free)
+                    th.start()
+                    th.join()
+                del saved
+    torch.cuda.synchronize()
 
 
 def test_work_hint_while_another_stream_writes_it(R):
