@@ -1121,6 +1121,7 @@ gsr_status gsr_graph_create(gsr_ctx* ctx, const gsr_gaussians* g, const gsr_came
   if ((st = forward_eager(ctx, g, cams, V, s, outs, &probe)) != GSR_OK) return st;
   const int64_t M = probe->M, NV = probe->n_vis;
   release(probe);
+  ctx->kept.clear(ctx->stream);  // (the pool has the measuring forward's memory for the graph's own)
   const int64_t VN = int64_t(V) * g->n;
   const int64_t cap_vis = std::min<int64_t>(VN, int64_t(std::ceil(double(NV) * (1.0 + headroom))) + 256);
   int64_t cap_M = int64_t(std::ceil(double(M) * (1.0 + headroom))) + 4096;
